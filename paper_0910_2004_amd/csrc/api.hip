@@ -1989,8 +1989,6 @@ kappa_status refine_impl(const DevGraph &d, int32_t *part, int32_t k, uint32_t e
                          hipStream_t s) {
     const int64_t n = d.n, maxp = std::max<int64_t>(1, (int64_t)k * (k - 1) / 2);
     RefineLaunch R{};
-    unsigned long long *qbits = nullptr;
-    int32_t *tmp_pair = nullptr, *tmp_col = nullptr;
     // the control block and the colour offsets, read back together
     struct Head {
         RefineCtl ctl;
@@ -2001,59 +1999,66 @@ kappa_status refine_impl(const DevGraph &d, int32_t *part, int32_t k, uint32_t e
     if (!carve_workspace(s, w, [&](Carve &cv) {
             head = cv.get<Head>(1);
             R.bw = cv.get<int64_t>(k);
-            R.bc = cv.get<int32_t>(k);
-            qbits = cv.get<unsigned long long>((int64_t)k * REFINE_QW);
-            tmp_pair = cv.get<int32_t>(maxp);
-            tmp_col = cv.get<int32_t>(maxp);
+            R.bd = cv.get<int64_t>(k);
+            R.bc = cv.get<int32_t>(2 * k);
+            R.qbits = cv.get<unsigned long long>((int64_t)k * REFINE_QW);
+            R.bcnt = cv.get<int32_t>(2 * k);
+            R.blo = cv.get<int32_t>(k + 1);
+            R.bme = cv.get<int32_t>(k);
+            R.tab = cv.get<uint8_t>((int64_t)k * REFINE_COLOURS);
             R.cpairs = cv.get<int32_t>(maxp);
-            R.fill = cv.get<int32_t>(maxp);
-            R.poff = cv.get<int32_t>(maxp);
-            R.region = cv.get<int32_t>(n);
-            R.dist = cv.get<int32_t>(n);
-            R.gain = cv.get<int64_t>(2 * n);
-            R.status = cv.get<uint8_t>(2 * n);
-            R.qlist = cv.get<int32_t>(2 * n);
+            R.ext = cv.get<uint16_t>(n);
+            R.blist = cv.get<int32_t>(n);
+            R.xlist = cv.get<int32_t>(n);
+            R.loc = cv.get<int32_t>(n);
+            R.alist = cv.get<int32_t>(n);
+            R.ldeg = cv.get<int32_t>(n);
+            R.key = cv.get<uint64_t>(2 * n);
             R.mlog = cv.get<int32_t>(2 * n);
-            R.slot = cv.get<int32_t>(2 * n);
+            R.lrow = cv.get<int2>(d.nnz);
         }))
         return KAPPA_E_NOMEM;
     R.xadj = d.xadj; R.adj = d.adj; R.ew = d.ew; R.vw = d.vw; R.part = part;
     R.n = d.n; R.k = k; R.eps_num = eps_num; R.eps_den = eps_den; R.seed = p->seed;
     R.alpha_num = p->alpha_num; R.alpha_den = p->alpha_den; R.depth = p->depth;
     R.max_local = p->max_local;
-    // KAPPA_REFINE_QCAP (tests): fewer on-chip queue entries, to exercise the
-    // entries kept in memory
+    // KAPPA_REFINE_QCAP (tests): a smaller on-chip capacity, to exercise the
+    // searches kept in memory.  On chip, row starts are 32-bit.
     const char *qc = getenv("KAPPA_REFINE_QCAP");
-    R.qcap = qc ? atoi(qc) : -1;
+    R.acap = qc ? atoi(qc) : -1;
+    if (d.nnz > (int64_t)UINT32_MAX) R.acap = 0;
     R.ctl = &head->ctl;
     R.col_off = head->col_off;
     {
         ZeroRanges z;
         z.add((uint32_t *)head, sizeof(Head) / 4);
         z.add((uint32_t *)R.bw, 2 * (int64_t)k);
+        z.add((uint32_t *)R.bd, 2 * (int64_t)k);
         z.add((uint32_t *)R.bc, k);
         launch_zero(z, s);
     }
-    launch_refine_weights(part, d.vw, d.n, k, R.bw, R.bc, R.ctl, s);
+    launch_refine_weights(R, s);
     Head *rb = (Head *)pinned(sizeof(Head));
     if (!rb) return KAPPA_E_NOMEM;
     kappa_refine_stats st{};
     unsigned long long adopted = 0;
     int32_t idle = 0;
     bool pending = false;   // launched searches whose outcome has not been read
+    int parity = 0;         // of the node counts (launch_refine_colour)
     for (int32_t gi = 0;; ++gi) {
         // the colouring of the next global iteration is launched before it is
         // known whether that iteration runs: one read-back per iteration
         if (gi < p->max_global) {
             ZeroRanges z;
-            z.add((uint32_t *)qbits, (int64_t)k * REFINE_QW * 2);
+            z.add((uint32_t *)R.qbits, (int64_t)k * REFINE_QW * 2);
+            z.add(R.bcnt, 2 * k);
             launch_zero(z, s);
-            launch_refine_colouring(d.xadj, d.adj, part, d.n, k, qbits, tmp_pair, tmp_col,
-                                    R.cpairs, R.col_off, R.fill, R.ctl, s);
+            launch_refine_colouring(R, parity, s);
         }
         HIPCHK(hipMemcpyAsync(rb, head, sizeof(Head), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         if (gi == 0 && (rb->ctl.flags & 1u)) return KAPPA_E_RANGE;
+        R.max_wd = rb->ctl.max_wd;
         if (rb->ctl.flags & 2u) {
             if (debug_on()) fprintf(stderr, "kappa: refine: block counts disagree with part\n");
             return KAPPA_E_HIP;
@@ -2069,8 +2074,11 @@ kappa_status refine_impl(const DevGraph &d, int32_t *part, int32_t k, uint32_t e
         st.global_iterations += 1;
         st.colours += ncol;
         for (int32_t c = 0; c < ncol; ++c)
-            if (rb->col_off[c + 1] > rb->col_off[c])
-                launch_refine_colour(R, gi, c, rb->col_off[c + 1] - rb->col_off[c], s);
+            if (rb->col_off[c + 1] > rb->col_off[c]) {
+                launch_refine_colour(R, gi, c, rb->col_off[c], rb->col_off[c + 1] - rb->col_off[c],
+                                     parity, s);
+                parity ^= 1;
+            }
         HIPCHK(hipGetLastError());
         pending = true;
     }

@@ -956,6 +956,8 @@ constexpr int REFINE_CW = REFINE_COLOURS / 64;
 struct RefineCtl {
     unsigned long long total;     // c(V)
     unsigned long long max_node;  // max_v c(v)
+    unsigned long long max_wd;    // the largest weighted degree
+    unsigned long long xn;        // entries of the later boundary list (above n: every node)
     uint32_t flags;               // 1: a block id outside [0, k); 2: block counts disagree with part
     int32_t ncol, npairs, pad;
     unsigned long long stats[8];  // [1] searches, [2] moves, [3] kept, [4] adoptions, [5] bytes,
@@ -973,26 +975,28 @@ struct RefineLaunch {
     uint64_t seed;
     uint32_t alpha_num, alpha_den;
     int32_t depth, max_local;
-    int32_t *cpairs, *col_off, *poff, *fill;
-    int64_t *bw;
-    int32_t *bc;
-    int32_t *region, *dist;
-    int64_t *gain;
-    uint8_t *status;
-    int32_t *qlist, *mlog, *slot;
-    int32_t qcap;   // queue entries per search kept on chip (-1: the kernel's maximum)
+    unsigned long long *qbits;         // k * REFINE_QW (zero before a colouring)
+    uint8_t *tab;                      // k * REFINE_COLOURS
+    int32_t *cpairs, *col_off;
+    int32_t *bcnt, *blo, *bme;         // 2 * k (zero before a colouring), k + 1, k
+    int64_t *bw, *bd;                  // k: block weights, degree sums
+    int32_t *bc;                       // 2 * k: node counts, by launch parity
+    uint16_t *ext;                     // n
+    int32_t *blist, *xlist, *loc, *alist, *ldeg, *mlog;   // n each, mlog 2 * n
+    uint64_t *key;                     // 2 * n
+    int2 *lrow;                        // nnz
+    uint64_t max_wd;                   // the largest weighted degree (read back)
+    int32_t acap;   // largest pair or search area kept on chip (-1: the kernel's maximum)
     RefineCtl *ctl;
 };
 
-void launch_refine_weights(const int32_t *part, const uint32_t *vw, int32_t n, int32_t k,
-                           int64_t *bw, int32_t *bc, RefineCtl *ctl, hipStream_t s);
-// Q of the current partition and its greedy colouring (qbits must be zero).
-void launch_refine_colouring(const int64_t *xadj, const int32_t *adj, const int32_t *part,
-                             int32_t n, int32_t k, unsigned long long *qbits, int32_t *tmp_pair,
-                             int32_t *tmp_col, int32_t *cpairs, int32_t *col_off, int32_t *fill,
-                             RefineCtl *ctl, hipStream_t s);
-// the local searches of colour c (npairs pairs) of global iteration gi
-void launch_refine_colour(const RefineLaunch &R, int32_t gi, int32_t c, int32_t npairs,
-                          hipStream_t s);
+void launch_refine_weights(const RefineLaunch &R, hipStream_t s);
+// Q of the current partition, its greedy colouring and the blocks' node lists
+// (qbits and bcnt must be zero).  parity: which half of bc holds the counts.
+void launch_refine_colouring(const RefineLaunch &R, int parity, hipStream_t s);
+// The local searches of colour c (its npairs pairs from p0 on in cpairs) of
+// global iteration gi; the other half of bc receives the counts.
+void launch_refine_colour(const RefineLaunch &R, int32_t gi, int32_t c, int32_t p0, int32_t npairs,
+                          int parity, hipStream_t s);
 
 }  // namespace kappa
