@@ -1820,9 +1820,8 @@ extern "C" kappa_status kappa_cut_balance(const kappa_graph *g, const int32_t *p
             tr = cv.get<int32_t>(tile_rows_needed(d.nnz));
         }))
         return KAPPA_E_NOMEM;
-    launch_up_clear(a, k, s);
-    launch_up_level(d, UP_GIVEN, nullptr, 0, nullptr, 0, const_cast<int32_t *>(part), k, eps_num,
-                    eps_den, tr, a, block_w, rd, s);
+    launch_up_clear(a, k, 1, s);
+    launch_cut_level(d, const_cast<int32_t *>(part), k, eps_num, eps_den, tr, a, block_w, rd, s);
     struct RB {
         kappa_cut_result r;
         uint32_t f;
@@ -1903,9 +1902,9 @@ extern "C" kappa_status kappa_cut_balance_noalloc(const kappa_graph *g, const in
     hipStream_t s = S(stream);
     const DevGraph d = dev(g);
     const CutScratch cs(base, k, d.nnz);
-    launch_up_clear(cs.a, k, s);   // a fill kernel: the scratch keeps the last call's contents
-    launch_up_level(d, UP_GIVEN, nullptr, 0, nullptr, 0, const_cast<int32_t *>(part), k, eps_num,
-                    eps_den, cs.tr, cs.a, block_w, cs.rd, s);
+    launch_up_clear(cs.a, k, 1, s);   // a fill kernel: the scratch keeps the last call's contents
+    launch_cut_level(d, const_cast<int32_t *>(part), k, eps_num, eps_den, cs.tr, cs.a, block_w,
+                     cs.rd, s);
     kappa_cut_result r;
     uint32_t flag = 0;
     HIPCHK(hipMemcpyAsync(&r, cs.rd, sizeof r, hipMemcpyDeviceToHost, s));
@@ -1923,23 +1922,26 @@ extern "C" kappa_status kappa_uncoarsen(const kappa_hierarchy *h, int32_t k, uin
     if (h->levels[0].n > 0 && !part0) return KAPPA_E_ARG;
     hipStream_t s = S(stream);
     const int32_t nl = (int32_t)h->levels.size();
-    std::vector<int32_t *> part(nl, nullptr);
+    std::vector<UpLevel> lv(nl);
+    for (int32_t l = 0; l < nl; ++l) {
+        const kappa_level &h_l = h->levels[l];
+        lv[l] = UpLevel{h_l.xadj, h_l.adj, h_l.ew, h_l.vw, h_l.cmap, nullptr, nullptr, h_l.nnz, h_l.n};
+    }
     kappa_cut_result *rd = nullptr;
     UpAcc a;
-    int32_t *tr = nullptr;
     std::unique_ptr<Workspace> w;
     if (!carve_workspace(s, w, [&](Carve &cv) {
-            for (int32_t l = 1; l < nl; ++l) part[l] = cv.get<int32_t>(h->levels[l].n);
+            for (int32_t l = 0; l < nl; ++l) {
+                lv[l].part = l > 0 ? cv.get<int32_t>(lv[l].n) : part0;
+                lv[l].tile_row = cv.get<int32_t>(tile_rows_needed(lv[l].nnz));
+            }
             rd = cv.get<kappa_cut_result>(nl);
-            a.bw = cv.get<uint64_t>((int64_t)BW_SHARDS * k);
-            a.acc = cv.get<uint64_t>(3 * NSHARD);
+            a.bw = cv.get<uint64_t>((int64_t)nl * BW_SHARDS * k);
+            a.acc = cv.get<uint64_t>((int64_t)nl * 3 * NSHARD);
             a.arrive = cv.get<unsigned>(ARRIVE_WORDS);
             a.flag = cv.get<uint32_t>(1);
-            tr = cv.get<int32_t>(tile_rows_needed(h->levels[0].nnz));
         }))
         return KAPPA_E_NOMEM;
-    part[0] = part0;
-    const int32_t L = nl - 1;
     std::vector<uint64_t> key = {2, pkey(w->base), (uint64_t)nl, (uint64_t)k, part_seed,
                                  (uint64_t)eps_num, (uint64_t)eps_den, pkey(part0)};
     for (const kappa_level &lv : h->levels) {
@@ -1952,18 +1954,8 @@ extern "C" kappa_status kappa_uncoarsen(const kappa_hierarchy *h, int32_t k, uin
         key.push_back(pkey(lv.cmap));
     }
     HIPCHK(run_seq(w->c, s, key, [&](hipStream_t q) {
-        launch_up_clear(a, k, q);
-        for (int32_t l = L; l >= 0; --l) {
-            const kappa_level &lv = h->levels[l];
-            DevGraph d;
-            d.n = lv.n; d.nnz = lv.nnz; d.xadj = lv.xadj; d.adj = lv.adj; d.ew = lv.ew; d.vw = lv.vw;
-            if (l == L)
-                launch_up_level(d, UP_INITIAL, nullptr, 0, nullptr, part_seed, part[l], k, eps_num,
-                                eps_den, tr, a, nullptr, rd + l, q);
-            else
-                launch_up_level(d, UP_PROJECT, lv.cmap, h->levels[l + 1].n, part[l + 1], 0, part[l],
-                                k, eps_num, eps_den, tr, a, nullptr, rd + l, q);
-        }
+        launch_up_clear(a, k, nl, q);
+        launch_way_up(lv.data(), nl, part_seed, k, eps_num, eps_den, a, rd, q);
     }));
     uint32_t *hf = (uint32_t *)pinned(sizeof(kappa_cut_result) * nl + 8, PIN_RESULTS);
     if (!hf) return KAPPA_E_ARG;

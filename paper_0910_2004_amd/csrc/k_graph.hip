@@ -7,6 +7,8 @@
 // row offsets of its tile in LDS and finds each entry's row by binary search
 // there.  Reads of adj/ew are fully coalesced and a node of any degree costs
 // the same per entry (power-law hubs spread over many tiles).
+#include <algorithm>
+
 #include "kappa_internal.h"
 
 namespace kappa {
@@ -613,65 +615,103 @@ void launch_project(const int32_t *cmap, int32_t n_fine, int32_t n_coarse,
 }
 
 // ---------------------------------------------------------------------------
-// One level of the way back up (Section 2: uncontraction, then cut and
-// balance; imbalance of Section 5.2), two kernels.
-//   up_nodes:   the level's partition (projected through cmap, or the
-//               stand-in initial partition, or given), block weights in an
-//               LDS histogram, c(V) and max c(v), the entry tiles' rows
-//   up_entries: the cut over entry tiles; the last block to finish sums the
-//               shards, writes the result and clears the accumulators for
-//               the next level
-// Accumulators (zero on entry, zero again on exit): bw[BW_SHARDS][k],
-// acc[3][NSHARD] (cut, c(V), max c(v)), arrive[ARRIVE_WORDS].
+// The way back up (Section 2: uncontraction, then cut and balance; imbalance
+// of Section 5.2), many levels per launch.
+//   up_nodes:   the partitions of a group of consecutive levels (a node
+//               follows its maps to the level above the group, or to the
+//               coarsest level, whose stand-in partition is a hash of the
+//               id; or given), block weights in an LDS histogram, c(V) and
+//               max c(v), the entry tiles' rows
+//   up_entries: the cuts of the levels of a table, over entry tiles
+//   up_finalize: per level, the shards summed and the exact L_max test
+// A level by itself took two dependent launches, each a chain of a few
+// dependent loads (5 and 11 us on levels of a few thousand nodes).  The only
+// dependency between levels is the partition, and following maps breaks it:
+// a random geometric graph of 2^20 nodes, 15 levels, 400 -> 140 us.
+// Accumulators (zero on entry, zero again on exit), per level: bw[BW_SHARDS][k],
+// acc[3][NSHARD] (cut, c(V), max c(v)); arrive[ARRIVE_WORDS] for the call.
 // flag bit 0: a map entry out of range; bit 1: a block id out of range.
 // ---------------------------------------------------------------------------
-constexpr int UP_NODE_BLOCKS = 512;
+constexpr int UP_NODE_BLOCKS = 512;   // blocks of a level at most (each adds its histogram)
+constexpr int UP_NODE_ITEMS = 4;      // nodes of a thread in flight
 
-__global__ void __launch_bounds__(BLOCK) up_nodes_k(DevGraph g, int mode, const int32_t *cmap,
-                                                    int32_t n_coarse, const int32_t *part_c,
-                                                    uint64_t part_seed, int32_t *part, int32_t k,
-                                                    int32_t *tile_row, uint64_t *bw, uint64_t *acc,
+// base_part: the partition of the level above the group's coarsest (base_n
+// nodes); null: the group's coarsest level gets the stand-in partition.
+// given: the (single) level's partition is in place.
+__global__ void __launch_bounds__(BLOCK) up_nodes_k(UpTable T, const int32_t *base_part,
+                                                    int32_t base_n, int given, uint64_t part_seed,
+                                                    int32_t k, uint64_t *bw, uint64_t *acc,
                                                     uint32_t *flag) {
     extern __shared__ uint64_t s_hist[];   // k entries
     __shared__ uint64_t sh[BLOCK / WAVE + 1];
     __shared__ uint32_t shm[BLOCK / WAVE];
+    int li = 0;   // this block's level
+    while (li + 1 < T.count && blockIdx.x >= T.first[li + 1]) ++li;
+    const UpLevel L = T.lv[li];
+    const unsigned bid = blockIdx.x - T.first[li], nb = T.first[li + 1] - T.first[li];
+    bw += (int64_t)(T.l0 + li) * BW_SHARDS * k;
+    acc += (int64_t)(T.l0 + li) * 3 * NSHARD;
     for (int i = threadIdx.x; i < k; i += blockDim.x) s_hist[i] = 0;
     __syncthreads();
-    const int64_t ntiles = etiles(g.nnz);
+    const int64_t ntiles = etiles(L.nnz);
+    const int hops = base_part ? T.count : T.count - 1;   // maps to follow end here
     uint64_t tot = 0;
     uint32_t mx = 0, bad = 0;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < g.n;
-         v += (int64_t)gridDim.x * blockDim.x) {
-        int32_t p;
-        if (mode == UP_PROJECT) {
-            const int32_t cx = cmap[v];
-            if (cx < 0 || cx >= n_coarse) {
-                p = -1;
-                bad |= 1u;
-            } else {
-                p = part_c[cx];
-            }
-            part[v] = p;
-        } else if (mode == UP_INITIAL) {
-            p = (int32_t)(mix64(part_seed + (uint64_t)v) % (uint64_t)k);
-            part[v] = p;
+    const int64_t stride = (int64_t)nb * BLOCK;
+    for (int64_t v0 = (int64_t)bid * BLOCK + threadIdx.x; v0 < L.n; v0 += stride * UP_NODE_ITEMS) {
+        int32_t x[UP_NODE_ITEMS];
+        uint32_t c[UP_NODE_ITEMS];
+        int64_t b[UP_NODE_ITEMS], e[UP_NODE_ITEMS];
+#pragma unroll
+        for (int q = 0; q < UP_NODE_ITEMS; ++q) {
+            const int64_t v = v0 + q * stride;
+            const bool in = v < L.n;
+            x[q] = in ? (int32_t)v : -1;
+            c[q] = in ? L.vw[v] : 0u;
+            b[q] = in ? L.xadj[v] : 0;
+            e[q] = in ? L.xadj[v + 1] : 0;
+        }
+        if (given) {
+#pragma unroll
+            for (int q = 0; q < UP_NODE_ITEMS; ++q) x[q] = x[q] >= 0 ? L.part[x[q]] : -1;
         } else {
-            p = part[v];
+            for (int h = li; h < hops; ++h) {   // block-uniform
+                const int32_t *cmap = T.lv[h].cmap;
+                const int32_t n_up = h + 1 < T.count ? T.lv[h + 1].n : base_n;
+#pragma unroll
+                for (int q = 0; q < UP_NODE_ITEMS; ++q) {
+                    if (x[q] < 0) continue;
+                    x[q] = cmap[x[q]];
+                    if ((uint32_t)x[q] >= (uint32_t)n_up) {
+                        x[q] = -1;
+                        bad |= 1u;
+                    }
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < UP_NODE_ITEMS; ++q)
+                if (x[q] >= 0)
+                    x[q] = base_part ? base_part[x[q]]
+                                     : (int32_t)(mix64(part_seed + (uint64_t)x[q]) % (uint64_t)k);
         }
-        const uint32_t c = g.vw[v];
-        if (p < 0 || p >= k) {
-            bad |= 2u;
-        } else if (c) {
-            atomicAdd((unsigned long long *)&s_hist[p], (unsigned long long)c);
+#pragma unroll
+        for (int q = 0; q < UP_NODE_ITEMS; ++q) {
+            const int64_t v = v0 + q * stride;
+            if (v >= L.n) continue;
+            if (!given) L.part[v] = x[q];
+            if (x[q] < 0 || x[q] >= k) {
+                bad |= 2u;
+            } else if (c[q]) {
+                atomicAdd((unsigned long long *)&s_hist[x[q]], (unsigned long long)c[q]);
+            }
+            tot += c[q];
+            mx = c[q] > mx ? c[q] : mx;
+            for (int64_t t = (b[q] + ETILE - 1) / ETILE; t * ETILE < e[q] && t < ntiles; ++t)
+                L.tile_row[t] = (int32_t)v;
         }
-        tot += c;
-        mx = c > mx ? c : mx;
-        const int64_t b = g.xadj[v], e = g.xadj[v + 1];
-        for (int64_t t = (b + ETILE - 1) / ETILE; t * ETILE < e && t < ntiles; ++t)
-            tile_row[t] = (int32_t)v;
     }
     __syncthreads();
-    uint64_t *bws = bw + (int64_t)(blockIdx.x % BW_SHARDS) * k;
+    uint64_t *bws = bw + (int64_t)(bid % BW_SHARDS) * k;
     for (int i = threadIdx.x; i < k; i += blockDim.x)
         if (s_hist[i]) atomicAdd((unsigned long long *)&bws[i], (unsigned long long)s_hist[i]);
     tot = block_sum(tot, sh);
@@ -681,7 +721,7 @@ __global__ void __launch_bounds__(BLOCK) up_nodes_k(DevGraph g, int mode, const 
     if (bad && lane_id() == 0) atomicOr(flag, bad);
     __syncthreads();
     if (threadIdx.x == 0) {
-        const int sd = shard_of_block();
+        const int sd = (int)(bid & (NSHARD - 1));
         for (int i = 1; i < BLOCK / WAVE; ++i) mx = shm[i] > mx ? shm[i] : mx;
         if (tot) atomicAdd((unsigned long long *)&acc[1 * NSHARD + sd], (unsigned long long)tot);
         if (mx) atomicMax((unsigned long long *)&acc[2 * NSHARD + sd], (unsigned long long)mx);
@@ -745,23 +785,45 @@ __device__ __forceinline__ void up_finalize(int32_t k, uint32_t eps_num, uint32_
     res->feasible = lhs <= lnum ? 1 : 0;
 }
 
-// LAST: the block that finishes last finalizes (small grids); otherwise
-// up_finalize_k runs next (a release per block costs more on large grids).
+// The cut over entry tiles; grid blocks walk the tiles of all levels of the
+// table.  Large levels are bound by the row searches and the tile's chain of
+// loads (R-MAT scale 22: 2.9 ms over all levels, the entries' bytes 0.7 ms at
+// copy rate), not by the gathers of part: with a byte per node instead of 32
+// bits 2.9 as well.  Rows of eight consecutive entries of a thread by one
+// search and a walk: 2.7 with bytes, 3.6 without, slower on R-MAT scale 18.
+// LAST (one level, small grids): the block that finishes last finalizes;
+// otherwise up_finalize_k runs next (a release per block costs more on large
+// grids).
 template <bool LAST>
-__global__ void __launch_bounds__(BLOCK) up_entries_k(DevGraph g, const int32_t *tile_row,
-                                                      const int32_t *part, int32_t k,
-                                                      uint32_t eps_num, uint32_t eps_den,
-                                                      uint64_t *bw, uint64_t *acc, unsigned *arrive,
-                                                      uint64_t *block_w_out,
+__global__ void __launch_bounds__(BLOCK) up_entries_k(UpTable T, int32_t k, uint32_t eps_num,
+                                                      uint32_t eps_den, uint64_t *bw, uint64_t *acc,
+                                                      unsigned *arrive, uint64_t *block_w_out,
                                                       kappa_cut_result *res) {
     __shared__ int64_t s_off[ETILE_ROWS + 1];
     __shared__ uint64_t sh[BLOCK / WAVE + 1];
     __shared__ uint64_t s_acc[3];
     __shared__ int last;
-    const int64_t ntiles = etiles(g.nnz);
     uint64_t cut = 0;
-    for (int64_t tt = blockIdx.x; tt < ntiles; tt += gridDim.x) {
-        TileCtx t = tile_begin(g, tile_row, tt, s_off);
+    int li = 0;
+    auto flush = [&]() {   // this block's part of level li's cut
+        cut = block_sum(cut, sh);
+        if (threadIdx.x == 0 && cut)
+            atomicAdd((unsigned long long *)&acc[(int64_t)(T.l0 + li) * 3 * NSHARD + shard_of_block()],
+                      (unsigned long long)cut);
+        cut = 0;
+    };
+    for (unsigned tt = blockIdx.x; tt < T.tiles[T.count]; tt += gridDim.x) {   // block-uniform
+        int l = li;
+        while (tt >= T.tiles[l + 1]) ++l;
+        if (l != li) {
+            flush();
+            li = l;
+        }
+        const UpLevel L = T.lv[li];
+        const int32_t *const part = L.part;
+        DevGraph g;
+        g.n = L.n; g.nnz = L.nnz; g.xadj = L.xadj; g.adj = L.adj; g.ew = L.ew; g.vw = L.vw;
+        const TileCtx t = tile_begin(g, L.tile_row, tt - T.tiles[li], s_off);
         int32_t vv[ETILE_ITEMS], uu[ETILE_ITEMS];
         uint32_t ww[ETILE_ITEMS];
 #pragma unroll
@@ -780,9 +842,7 @@ __global__ void __launch_bounds__(BLOCK) up_entries_k(DevGraph g, const int32_t 
         for (int i = 0; i < ETILE_ITEMS; ++i)
             if (uu[i] > vv[i] && part[uu[i]] != part[vv[i]]) cut += ww[i];
     }
-    cut = block_sum(cut, sh);
-    if (threadIdx.x == 0 && cut)
-        atomicAdd((unsigned long long *)&acc[shard_of_block()], (unsigned long long)cut);
+    flush();
     if (!LAST) return;
     __syncthreads();
     if (threadIdx.x == 0) last = arrive_last(arrive);
@@ -791,48 +851,117 @@ __global__ void __launch_bounds__(BLOCK) up_entries_k(DevGraph g, const int32_t 
     up_finalize(k, eps_num, eps_den, bw, acc, block_w_out, res, sh, s_acc);
 }
 
+// One block per level.
 __global__ void __launch_bounds__(BLOCK) up_finalize_k(int32_t k, uint32_t eps_num,
                                                        uint32_t eps_den, uint64_t *bw,
                                                        uint64_t *acc, uint64_t *block_w_out,
                                                        kappa_cut_result *res) {
     __shared__ uint64_t sh[BLOCK / WAVE + 1];
     __shared__ uint64_t s_acc[3];
-    up_finalize(k, eps_num, eps_den, bw, acc, block_w_out, res, sh, s_acc);
+    const int64_t l = blockIdx.x;
+    up_finalize(k, eps_num, eps_den, bw + l * BW_SHARDS * k, acc + l * 3 * NSHARD, block_w_out,
+                res + l, sh, s_acc);
 }
 
 constexpr unsigned UP_LAST_BLOCKS = 64;   // grids up to this size finalize in their last block
+constexpr unsigned UP_ENTRY_BLOCKS = 4096;
 
-void launch_up_level(const DevGraph &g, int mode, const int32_t *cmap, int32_t n_coarse,
-                     const int32_t *part_c, uint64_t part_seed, int32_t *part, int32_t k,
-                     uint32_t eps_num, uint32_t eps_den, int32_t *tile_row, const UpAcc &a,
-                     uint64_t *block_w_out, kappa_cut_result *res, hipStream_t s) {
-    {
-        KAPPA_PROF("up_nodes", s);
-        hipLaunchKernelGGL(up_nodes_k, dim3(grid_for(g.n, BLOCK * 4, UP_NODE_BLOCKS)), dim3(BLOCK),
-                           (size_t)k * sizeof(uint64_t), s, g, mode, cmap, n_coarse, part_c,
-                           part_seed, part, k, tile_row, a.bw, a.acc, a.flag);
-    }
-    const unsigned grid = grid_for(etiles(g.nnz), 1, ARRIVE_MAX_BLOCKS);
-    if (grid <= UP_LAST_BLOCKS) {
+static void up_nodes(UpTable &T, const int32_t *base_part, int32_t base_n, bool given,
+                     uint64_t part_seed, int32_t k, const UpAcc &a, hipStream_t s) {
+    T.first[0] = 0;
+    for (int i = 0; i < T.count; ++i)
+        T.first[i + 1] = T.first[i] + grid_for(T.lv[i].n, BLOCK * UP_NODE_ITEMS, UP_NODE_BLOCKS);
+    KAPPA_PROF("up_nodes", s);
+    hipLaunchKernelGGL(up_nodes_k, dim3(T.first[T.count]), dim3(BLOCK),
+                       (size_t)k * sizeof(uint64_t), s, T, base_part, base_n, given ? 1 : 0,
+                       part_seed, k, a.bw, a.acc, a.flag);
+}
+
+// The table's tile counts (below 2^32: a level has fewer than 2^31 tiles);
+// returns the total.
+static unsigned up_tiles(UpTable &T) {
+    T.tiles[0] = 0;
+    for (int i = 0; i < T.count; ++i) T.tiles[i + 1] = T.tiles[i] + (uint32_t)etiles(T.lv[i].nnz);
+    return T.tiles[T.count];
+}
+
+void launch_cut_level(const DevGraph &g, int32_t *part, int32_t k, uint32_t eps_num,
+                      uint32_t eps_den, int32_t *tile_row, const UpAcc &a, uint64_t *block_w_out,
+                      kappa_cut_result *res, hipStream_t s) {
+    UpTable T;
+    T.count = 1;
+    T.l0 = 0;
+    T.lv[0] = UpLevel{g.xadj, g.adj, g.ew, g.vw, nullptr, part, tile_row, g.nnz, g.n};
+    up_nodes(T, nullptr, 0, true, 0, k, a, s);
+    const unsigned tiles = up_tiles(T);
+    if (tiles <= UP_LAST_BLOCKS) {
         KAPPA_PROF("up_entries", s);
-        hipLaunchKernelGGL(up_entries_k<true>, dim3(grid), dim3(BLOCK), 0, s, g, tile_row, part, k,
+        hipLaunchKernelGGL(up_entries_k<true>, dim3(tiles ? tiles : 1), dim3(BLOCK), 0, s, T, k,
                            eps_num, eps_den, a.bw, a.acc, a.arrive, block_w_out, res);
         return;
     }
     {
         KAPPA_PROF("up_entries", s);
-        hipLaunchKernelGGL(up_entries_k<false>, dim3(grid), dim3(BLOCK), 0, s, g, tile_row, part,
-                           k, eps_num, eps_den, a.bw, a.acc, a.arrive, block_w_out, res);
+        hipLaunchKernelGGL(up_entries_k<false>, dim3(std::min(tiles, UP_ENTRY_BLOCKS)), dim3(BLOCK),
+                           0, s, T, k, eps_num, eps_den, a.bw, a.acc, a.arrive, block_w_out, res);
     }
     KAPPA_PROF("up_finalize", s);
     hipLaunchKernelGGL(up_finalize_k, dim3(1), dim3(BLOCK), 0, s, k, eps_num, eps_den, a.bw, a.acc,
                        block_w_out, res);
 }
 
-void launch_up_clear(const UpAcc &a, int32_t k, hipStream_t s) {
+void launch_way_up(const UpLevel *lv, int32_t nl, uint64_t part_seed, int32_t k, uint32_t eps_num,
+                   uint32_t eps_den, const UpAcc &a, kappa_cut_result *res, hipStream_t s) {
+    // Partitions, from the coarsest level down, in groups of levels whose nodes
+    // follow their maps to the group's base together.  A further level costs its
+    // nodes times the maps they follow, a group of its own another launch and
+    // its latency (about 6 us); a random gather runs at about one per compute
+    // unit and cycle while the maps stay in cache, 6 us for UP_HOPS of them.
+    constexpr int64_t UP_HOPS = 4 << 20;
+    for (int32_t top = nl - 1; top >= 0;) {
+        const bool base = top + 1 < nl;   // the level above the group is done
+        int32_t fine = top;
+        int64_t hops = lv[top].n;
+        while (fine > 0 && top - fine + 1 < UP_TABLE) {
+            const int64_t more = (int64_t)lv[fine - 1].n * (top - (fine - 1) + (base ? 1 : 0));
+            if (hops + more > UP_HOPS) break;
+            hops += more;
+            --fine;
+        }
+        UpTable T;
+        T.count = top - fine + 1;
+        T.l0 = fine;
+        for (int i = 0; i < T.count; ++i) T.lv[i] = lv[fine + i];
+        up_nodes(T, base ? lv[top + 1].part : nullptr, base ? lv[top + 1].n : 0, false, part_seed, k,
+                 a, s);
+        top = fine - 1;
+    }
+    // cuts of all levels, as many as a table and its tile counts hold at a time
+    for (int32_t l = 0; l < nl;) {
+        UpTable T;
+        T.count = 0;
+        T.l0 = l;
+        int64_t tiles = 0;
+        while (l < nl && T.count < UP_TABLE &&
+               (T.count == 0 || tiles + etiles(lv[l].nnz) < ((int64_t)1 << 31))) {
+            tiles += etiles(lv[l].nnz);
+            T.lv[T.count++] = lv[l++];
+        }
+        if (up_tiles(T) == 0) continue;
+        KAPPA_PROF("up_entries", s);
+        hipLaunchKernelGGL(up_entries_k<false>, dim3(std::min(T.tiles[T.count], UP_ENTRY_BLOCKS)),
+                           dim3(BLOCK), 0, s, T, k, eps_num, eps_den, a.bw, a.acc, a.arrive,
+                           (uint64_t *)nullptr, res);
+    }
+    KAPPA_PROF("up_finalize", s);
+    hipLaunchKernelGGL(up_finalize_k, dim3(nl), dim3(BLOCK), 0, s, k, eps_num, eps_den, a.bw, a.acc,
+                       (uint64_t *)nullptr, res);
+}
+
+void launch_up_clear(const UpAcc &a, int32_t k, int32_t nl, hipStream_t s) {
     ZeroRanges z;
-    z.add(a.bw, (int64_t)BW_SHARDS * k * 2);
-    z.add(a.acc, 3 * NSHARD * 2);
+    z.add(a.bw, (int64_t)nl * BW_SHARDS * k * 2);
+    z.add(a.acc, (int64_t)nl * 3 * NSHARD * 2);
     z.add(a.arrive, ARRIVE_WORDS);
     z.add(a.flag, 1);
     launch_zero(z, s);

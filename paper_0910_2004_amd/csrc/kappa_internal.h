@@ -844,25 +844,48 @@ void launch_initial_partition(int32_t n, int32_t k, uint64_t seed, int32_t *part
 void launch_project(const int32_t *cmap, int32_t n_fine, int32_t n_coarse,
                     const int32_t *part_coarse, int32_t *part_fine, uint32_t *flag,
                     hipStream_t s);
-// One level of the way back up: the level's partition (mode: UP_GIVEN reads
-// part, UP_PROJECT writes part[v] = part_c[cmap[v]], UP_INITIAL writes the
-// stand-in part[v] = mix64(part_seed + v) mod k), then cut and balance into
-// res (device).  block_w_out (device [k], may be null) receives the block
-// weights.  The accumulators in `a` are zero on entry and left zero
-// (launch_up_clear zeroes them once).  tile_row: tile_rows_needed(g.nnz).
-enum UpMode { UP_GIVEN = 0, UP_PROJECT = 1, UP_INITIAL = 2 };
+// Levels of the way back up (device pointers): graph, map to the next level
+// (null on the coarsest), partition, tile rows (tile_rows_needed(nnz)).  A
+// launch takes a table of up to UP_TABLE consecutive levels, finest first, as
+// an argument: lv[i] is level l0 + i, its accumulators lie at that index;
+// first: the levels' first blocks, tiles: their first entry tiles.
+struct UpLevel {
+    const int64_t *xadj;
+    const int32_t *adj;
+    const uint32_t *ew;
+    const uint32_t *vw;
+    const int32_t *cmap;
+    int32_t *part;
+    int32_t *tile_row;
+    int64_t nnz;
+    int32_t n;
+};
+constexpr int UP_TABLE = 24;
+struct UpTable {
+    UpLevel lv[UP_TABLE];
+    uint32_t first[UP_TABLE + 1], tiles[UP_TABLE + 1];
+    int32_t count, l0;
+};
 constexpr int BW_SHARDS = 8;
-struct UpAcc {
-    uint64_t *bw;      // BW_SHARDS * k
-    uint64_t *acc;     // 3 * NSHARD
+struct UpAcc {             // nl levels
+    uint64_t *bw;      // nl * BW_SHARDS * k
+    uint64_t *acc;     // nl * 3 * NSHARD
     unsigned *arrive;  // ARRIVE_WORDS
     uint32_t *flag;    // 1: bit 0 map entry, bit 1 block id out of range
 };
-void launch_up_level(const DevGraph &g, int mode, const int32_t *cmap, int32_t n_coarse,
-                     const int32_t *part_c, uint64_t part_seed, int32_t *part, int32_t k,
-                     uint32_t eps_num, uint32_t eps_den, int32_t *tile_row, const UpAcc &a,
-                     uint64_t *block_w_out, kappa_cut_result *res, hipStream_t s);
-void launch_up_clear(const UpAcc &a, int32_t k, hipStream_t s);
+// Cut and balance of the partition part of g into res (device); block_w_out
+// (device [k], may be null) receives the block weights.  The accumulators
+// (of one level) are zero on entry and left zero (launch_up_clear zeroes them
+// once).
+void launch_cut_level(const DevGraph &g, int32_t *part, int32_t k, uint32_t eps_num,
+                      uint32_t eps_den, int32_t *tile_row, const UpAcc &a, uint64_t *block_w_out,
+                      kappa_cut_result *res, hipStream_t s);
+// The way back up over nl levels (finest first): the stand-in partition on the
+// coarsest (part[v] = mix64(part_seed + v) mod k), projections below it, cut
+// and balance of every level into res[l].
+void launch_way_up(const UpLevel *lv, int32_t nl, uint64_t part_seed, int32_t k, uint32_t eps_num,
+                   uint32_t eps_den, const UpAcc &a, kappa_cut_result *res, hipStream_t s);
+void launch_up_clear(const UpAcc &a, int32_t k, int32_t nl, hipStream_t s);
 // Level-resident variants of Out(v) (innerOuter): read level l's graph from the
 // descriptor; run only while level l is matching.
 void launch_level_out(const Ctx &c, int l, int64_t nnz_cap, int32_t n_hint, hipStream_t s);
