@@ -1596,13 +1596,15 @@ extern "C" kappa_status kappa_rcb_order(const double *xy, int32_t n, int32_t lea
     if (n < 0 || leaf < 1 || (n > 0 && (!xy || !order))) return KAPPA_E_ARG;
     hipStream_t s = S(stream);
     size_t need = 0;
-    kappa_status st = rcb_order_impl(xy, n, leaf, order, s, nullptr, 0, &need);
+    kappa_status st = rcb_order_impl(xy, n, leaf, order, s, nullptr, 0, &need, nullptr);
     if (st != KAPPA_OK) return st;
+    uint32_t *hflag = (uint32_t *)pinned(2 * sizeof(uint32_t));
+    if (!hflag) return KAPPA_E_NOMEM;
     char *buf = nullptr;
     std::unique_ptr<Workspace> w;
     if (!carve_workspace(s, w, [&](Carve &cv) { buf = cv.get<char>((int64_t)need); }))
         return KAPPA_E_NOMEM;
-    return rcb_order_impl(xy, n, leaf, order, s, buf, need, &need);
+    return rcb_order_impl(xy, n, leaf, order, s, buf, need, &need, hflag);
 }
 
 extern "C" kappa_status kappa_relabel(const kappa_graph *g, const int32_t *order,
@@ -1618,7 +1620,7 @@ extern "C" kappa_status kappa_relabel(const kappa_graph *g, const int32_t *order
     kappa_status st = relabel_impl(d, order, out->xadj, out->adj, out->ew, out->vw, s, nullptr, 0,
                                    &need, nullptr);
     if (st != KAPPA_OK) return st;
-    uint32_t *hflag = (uint32_t *)pinned(sizeof(uint32_t));
+    uint32_t *hflag = (uint32_t *)pinned(4 * sizeof(uint32_t));
     if (!hflag) return KAPPA_E_NOMEM;
     char *buf = nullptr;
     std::unique_ptr<Workspace> w;

@@ -957,7 +957,8 @@ kappa_status exclusive_sum_i64(const int64_t *in, int64_t *out, int64_t n, char 
 // and the relabelling of a graph by an order (k_relabel.hip).  ws == nullptr
 // asks for the workspace size only (*need).  Both synchronise the stream.
 kappa_status rcb_order_impl(const double *xy, int32_t n, int32_t leaf, int32_t *order,
-                            hipStream_t s, char *ws, size_t ws_bytes, size_t *need);
+                            hipStream_t s, char *ws, size_t ws_bytes, size_t *need,
+                            uint32_t *hflag);
 kappa_status relabel_impl(const DevGraph &g, const int32_t *order, int64_t *nx, int32_t *nadj,
                           uint32_t *new_ew, uint32_t *nvw, hipStream_t s, char *ws,
                           size_t ws_bytes, size_t *need, uint32_t *hflag);
