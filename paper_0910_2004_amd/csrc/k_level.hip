@@ -3424,29 +3424,48 @@ __global__ void batch_check_k(DevGraph g, uint32_t *flags) {
     if (__ballot(bad) && lane_id() == 0) atomicOr(flags, 1u);
 }
 
-// One graph's level out of a batch level: node range [a, b) of the union,
-// entries from ea; ids made local (cmap relative to the graph's first node
-// on the next level, cbase; cmap null on the coarsest level).
-__global__ void batch_extract_k(DevGraph u, const int32_t *cmap, const int32_t *mate, int32_t a,
-                                int32_t b, int64_t ea, int32_t cbase, int64_t *xadj, int32_t *adj,
-                                uint32_t *ew, uint32_t *vw, int32_t *cmap_out, int32_t *mate_out) {
-    const int32_t n = b - a;
-    const int64_t nnz = u.xadj[b] - ea;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= n; i += stride) {
-        xadj[i] = u.xadj[a + i] - ea;
-        if (i == n) continue;
-        vw[i] = u.vw[a + i];
-        if (cmap) cmap_out[i] = cmap[a + i] - cbase;
-        if (mate) {
-            const int32_t m = mate[a + i];
-            mate_out[i] = m >= 0 ? m - a : -1;
+// One graph's levels out of a batch, all in one launch (a copy of a few KB per
+// level: 10 levels one by one were 35 us of launches).  Blocks first[l] and up
+// take level l.
+constexpr int XTABLE = 16;
+struct BatchTable {
+    BatchExtract lv[XTABLE];
+    uint32_t first[XTABLE + 1];
+    int32_t count;
+};
+__global__ void __launch_bounds__(BLOCK) batch_extract_k(BatchTable T) {
+    int l = 0;
+    while (l + 1 < T.count && blockIdx.x >= T.first[l + 1]) ++l;
+    const BatchExtract x = T.lv[l];
+    const int64_t stride = (int64_t)(T.first[l + 1] - T.first[l]) * blockDim.x;
+    const int64_t t0 = (int64_t)(blockIdx.x - T.first[l]) * blockDim.x + threadIdx.x;
+    for (int64_t i = t0; i <= x.n; i += stride) {
+        x.xadj_out[i] = x.xadj[x.a + i] - x.ea;
+        if (i == x.n) continue;
+        x.vw_out[i] = x.vw[x.a + i];
+        if (x.cmap) x.cmap_out[i] = x.cmap[x.a + i] - x.cbase;
+        if (x.mate) {
+            const int32_t m = x.mate[x.a + i];
+            x.mate_out[i] = m >= 0 ? m - x.a : -1;
         }
     }
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < nnz; j += stride) {
-        adj[j] = u.adj[ea + j] - a;
-        ew[j] = u.ew[ea + j];
+    for (int64_t j = t0; j < x.nnz; j += stride) {
+        x.adj_out[j] = x.adj[x.ea + j] - x.a;
+        x.ew_out[j] = x.ew[x.ea + j];
     }
+}
+
+// The first entry of every graph on the levels of a table: the host reads those
+// of a whole batch at once.
+struct EoffTable {
+    const int64_t *xadj[XTABLE];
+};
+__global__ void __launch_bounds__(BLOCK) batch_eoff_k(EoffTable T, const int32_t *noff,
+                                                      int32_t count, int64_t *eoff) {
+    const int64_t at = (int64_t)blockIdx.y * ((int64_t)count + 1);
+    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g <= count;
+         g += (int64_t)gridDim.x * blockDim.x)
+        eoff[at + g] = T.xadj[blockIdx.y][noff[at + g]];
 }
 
 // Served steps: level j of every graph of a step's union, with ids made
@@ -4009,14 +4028,31 @@ void launch_batch_gid(const int32_t *noff, int32_t count, int32_t n, int32_t *gi
                        count, n, gid);
 }
 
-void launch_batch_extract(const DevGraph &u, const int32_t *cmap, const int32_t *mate, int32_t a,
-                          int32_t b, int64_t ea, int64_t nnz, int32_t cbase, int64_t *xadj,
-                          int32_t *adj, uint32_t *ew, uint32_t *vw, int32_t *cmap_out,
-                          int32_t *mate_out, hipStream_t s) {
-    KAPPA_PROF("batch_extract", s);
-    hipLaunchKernelGGL(batch_extract_k, dim3(grid_for(std::max<int64_t>(nnz, b - a + 1), BLOCK, 4096)),
-                       dim3(BLOCK), 0, s, u, cmap, mate, a, b, ea, cbase, xadj, adj, ew, vw,
-                       cmap_out, mate_out);
+void launch_batch_extract(const BatchExtract *x, int32_t nl, hipStream_t s) {
+    for (int32_t l = 0; l < nl; l += XTABLE) {
+        BatchTable T;
+        T.count = std::min<int32_t>(XTABLE, nl - l);
+        T.first[0] = 0;
+        for (int32_t i = 0; i < T.count; ++i) {
+            T.lv[i] = x[l + i];
+            T.first[i + 1] = T.first[i] +
+                             grid_for(std::max<int64_t>(x[l + i].nnz, (int64_t)x[l + i].n + 1), BLOCK, 4096);
+        }
+        KAPPA_PROF("batch_extract", s);
+        hipLaunchKernelGGL(batch_extract_k, dim3(T.first[T.count]), dim3(BLOCK), 0, s, T);
+    }
+}
+
+void launch_batch_eoff(const int64_t *const *xadj, int32_t nl, const int32_t *noff, int32_t count,
+                       int64_t *eoff, hipStream_t s) {
+    for (int32_t l = 0; l < nl; l += XTABLE) {
+        EoffTable T;
+        const int32_t c = std::min<int32_t>(XTABLE, nl - l);
+        for (int32_t i = 0; i < c; ++i) T.xadj[i] = xadj[l + i];
+        const int64_t at = (int64_t)l * ((int64_t)count + 1);
+        hipLaunchKernelGGL(batch_eoff_k, dim3(grid_for((int64_t)count + 1, BLOCK, 64), c), dim3(BLOCK),
+                           0, s, T, noff + at, count, eoff + at);
+    }
 }
 
 void launch_batch_check(const DevGraph &g, uint32_t *flags, hipStream_t s) {

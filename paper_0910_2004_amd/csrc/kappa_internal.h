@@ -929,10 +929,26 @@ void launch_serve_extract(const DevGraph &u1, const int32_t *noff1, int32_t coun
                           int32_t *dmax, hipStream_t s);
 // Copies nodes [a, b) of union level u (entries from ea, nnz of them) with
 // ids made local; cmap/mate (may be null) shifted as well.
-void launch_batch_extract(const DevGraph &u, const int32_t *cmap, const int32_t *mate, int32_t a,
-                          int32_t b, int64_t ea, int64_t nnz, int32_t cbase, int64_t *xadj,
-                          int32_t *adj, uint32_t *ew, uint32_t *vw, int32_t *cmap_out,
-                          int32_t *mate_out, hipStream_t s);
+// One graph's level out of a batch level: n nodes of the union from a, nnz
+// entries from ea; ids made local (cmap relative to the graph's first node on
+// the next level, cbase; cmap and mate null on the coarsest level).
+struct BatchExtract {
+    const int64_t *xadj;
+    const int32_t *adj;
+    const uint32_t *ew, *vw;
+    const int32_t *cmap, *mate;
+    int64_t *xadj_out;
+    int32_t *adj_out;
+    uint32_t *ew_out, *vw_out;
+    int32_t *cmap_out, *mate_out;
+    int64_t ea, nnz;
+    int32_t a, n, cbase;
+};
+void launch_batch_extract(const BatchExtract *x, int32_t nl, hipStream_t s);
+// eoff[l * (count + 1) + g] = xadj[l][noff[l * (count + 1) + g]] (xadj: host
+// table of device arrays).
+void launch_batch_eoff(const int64_t *const *xadj, int32_t nl, const int32_t *noff, int32_t count,
+                       int64_t *eoff, hipStream_t s);
 
 // Matching only (first kernel: the level gate, which moves an idle level to
 // PH_MATCH unless a stop rule fires; stop_rules = false checks none), e.g.
