@@ -148,7 +148,8 @@ typedef struct {
     int64_t matched;     /* |M| of this level's matching */
     int32_t stop_reason; /* kappa_stop; nonzero only on the coarsest level */
     int32_t grid_rounds; /* of those rounds, how many ran as grid-wide kernel launches (the
-                            rest ran in one workgroup once few nodes were pending); 0 in a
+                            rest ran in one workgroup once few nodes were pending); all of
+                            them on a small level that ran whole in one launch; 0 in a
                             hierarchy taken out of a batch */
 } kappa_level_info;
 

@@ -1004,6 +1004,15 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
     // If it did not take that level, the next batch runs the level in full.
     const bool tail_on = !bi && g_tail_on && c.block_bits < 0;
     int tail_end = -1;   // level at which the previous batch ended on a tail launch
+    // Small levels in one workgroup's LDS (k_small.hip), likewise: tried ahead
+    // of each level estimated within a factor 4 of its limits (a launch that
+    // takes nothing costs 3 us, a level it takes saves 50), ending the batch
+    // where the estimate fits or nearly (levels lose entries faster than
+    // nodes; a further level launched for nothing costs 70 us, the read-back
+    // 30).  A row too long for it stays so on coarser levels, so a graph with
+    // one keeps to the grid.
+    const bool small_on = !bi && !g_tail_on && c.block_bits < 0 && maxdeg0 <= SMALL_DEG;
+    double deg = n0 > 0 ? (double)d0.nnz / n0 : 0.0;   // entries per node of the newest level known
     // a level whose finisher handed it back (CF_EXTEND): the next batch
     // starts by giving it more grid rounds after round ext_round
     int ext_level = -1, ext_round = 0, ext_times = 0, ext_seen = -1;
@@ -1020,6 +1029,8 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
         int next = l_end;
         uint64_t ratio_bits;
         std::memcpy(&ratio_bits, &hint.ratio, sizeof ratio_bits);
+        uint64_t deg_bits;
+        std::memcpy(&deg_bits, &deg, sizeof deg_bits);
         const std::vector<uint64_t> key = {1, pkey(w->base), (uint64_t)n0, (uint64_t)d0.nnz,
                                            (uint64_t)hint.known_l, (uint64_t)hint.known_n, ratio_bits,
                                            (uint64_t)p->rating, p->seed, (uint64_t)maxl,
@@ -1028,7 +1039,7 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
                                            (uint64_t)(int64_t)tail_end,
                                            (uint64_t)(int64_t)c.block_bits,
                                            (uint64_t)(int64_t)ext_level, (uint64_t)ext_round,
-                                           (uint64_t)begin_only};
+                                           (uint64_t)begin_only, (uint64_t)small_on, deg_bits};
         HIPCHK(run_seq(w->c, s, key, [&](hipStream_t q) {
             if (begin_only) {
                 launch_batch_begin(c, launched, q);
@@ -1048,6 +1059,14 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
                     next = l;
                     break;
                 }
+                const double eh = deg * nh;
+                if (small_on && l != tail_end && nh <= 4 * SMALL_N && eh <= 4 * SMALL_E) {
+                    launch_small_levels(c, l, q);
+                    if (2 * nh <= 3 * SMALL_N && 2 * (eh + nh) <= 3 * SMALL_E) {
+                        next = l;
+                        break;
+                    }
+                }
                 // innerOuter on unit input weights ranks edges by degree
                 // sums, which chains level 0 over many rounds (17 grid rounds
                 // on the random geometric graph of 2^20 nodes); the finisher
@@ -1057,10 +1076,14 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
                 launch_level(c, l, nh, d0.nnz, n0, rounds, q);
             }
         }));
-        if (next < l_end && !begin_only) tail_end = next;
+        const bool tail_last = next < l_end && !begin_only;
         launched = next;
         HIPCHK(hipMemcpyAsync(hc, c.ctrl, sizeof(Control), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
+        // levels the small form finished before one that did not fit
+        if (small_on && tail_last) launched = std::max(launched, hc->nlevels - 1);
+        if (tail_last) tail_end = launched;
+        if (hc->last_n > 0) deg = (double)hc->last_nnz / hc->last_n;
         hint.seen(hc->nlevels - 1, hc->last_n);
         ext_level = -1;
         if ((hc->flags & CF_EXTEND) && !(hc->flags & ~(uint32_t)CF_EXTEND)) {

@@ -77,33 +77,6 @@ __device__ __forceinline__ int32_t checked_node(int32_t v, int32_t n, Control *c
 }
 
 // ===========================================================================
-// Level start (first kernel of a level): stop rules (Section 2 threshold,
-// Section 4), state resets.  Every block takes the same decision from the
-// same inputs; block 0 writes it (the only fields it changes are read as
-// "this level goes on" either way, or end the level for every block).
-// ===========================================================================
-__device__ __forceinline__ bool level_gate(const Ctx &c, int l, bool stop_rules, bool writer) {
-    Control *ctrl = c.ctrl;
-    LevelDesc *L = c.lv + l;
-    if (ctrl->done || ctrl->nlevels != l + 1) return false;
-    const int32_t ph = L->phase;
-    if (ph != PH_IDLE && ph != PH_MATCH) return false;
-    int32_t stop = KAPPA_STOP_NONE;
-    if (stop_rules && L->n <= ctrl->stop_n) stop = KAPPA_STOP_SIZE;
-    else if (stop_rules && l >= ctrl->max_levels) stop = KAPPA_STOP_MAXLEVEL;
-    if (stop != KAPPA_STOP_NONE || !L->mate || !L->cmap) {
-        if (writer) {
-            L->stop = stop;
-            L->phase = PH_STOPPED;
-            ctrl->done = 1;
-        }
-        return false;
-    }
-    if (writer) L->phase = PH_MATCH;
-    return true;
-}
-
-// ===========================================================================
 // Matching
 // ===========================================================================
 // Pending nodes of a round live in lists per degree bin, stored as three
@@ -260,15 +233,6 @@ __device__ __forceinline__ Cand scan_row_small(const DevGraph &g, int32_t v, uin
     return best;
 }
 
-template <int G>
-__device__ __forceinline__ Cand group_reduce(Cand cd, int32_t v) {
-    for (int off = G / 2; off > 0; off >>= 1) {
-        Cand o = cand_shfl_xor(cd, off, G);
-        if (cand_better(o, cd, v)) cd = o;
-    }
-    return cd;
-}
-
 // Whole-block argmax (all threads call; contains barriers).
 __device__ __forceinline__ Cand block_reduce_cand(Cand cd, int32_t v, Cand *sh) {
     cd = group_reduce<WAVE>(cd, v);
@@ -286,10 +250,6 @@ __device__ __forceinline__ Cand block_reduce_cand(Cand cd, int32_t v, Cand *sh) 
 // sets only shrink, so it is still the maximum).
 __device__ __forceinline__ bool keeps_choice(int32_t bp, int32_t n, const int2 *nrec) {
     return bp >= 0 && bp < n && nrec[bp].y < 0;
-}
-
-__device__ __forceinline__ uint64_t level_seed(const Ctx &c, int l) {
-    return c.seed_direct ? c.seed : mix64(c.seed + (uint64_t)l);
 }
 
 // The tie-break seed of v's graph: in a served step every graph carries the
@@ -1590,29 +1550,7 @@ struct RepF {
         return (m < 0 || i < m) ? 1 : 0;
     }
     __device__ void post(int64_t nc) const {
-        LevelDesc *L = c.lv + l, *N = c.lv + l + 1;
-        if (L->phase != PH_CONTRACT) return;
-        const bool batch = L->gid != nullptr;
-        const uint64_t b4 = (uint64_t)nc * 4;
-        const uint64_t bytes[6] = {b4, (uint64_t)(nc + 1) * 8, b4, b4, batch ? b4 : 0,
-                                   batch ? (uint64_t)(c.b.count + 1) * 4 : 0};
-        void *p[6];
-        const bool ok = arena_alloc_k<6>(c.ctrl, bytes, p);
-        N->n = (int32_t)nc;
-        N->vw = (uint32_t *)p[0];
-        N->xadj = (int64_t *)p[1];
-        N->mate = (int32_t *)p[2];
-        N->cmap = (int32_t *)p[3];
-        N->gid = batch ? (int32_t *)p[4] : nullptr;
-        N->noff = batch ? (int32_t *)p[5] : nullptr;
-        N->adj = nullptr;
-        N->ew = nullptr;
-        N->phase = PH_IDLE;
-        N->stop = KAPPA_STOP_NONE;
-        if (!ok) {
-            L->phase = PH_STOPPED;
-            c.ctrl->done = 1;
-        }
+        coarse_nodes(c, l, nc);
     }
 };
 struct RepW {
@@ -1677,39 +1615,7 @@ struct DegF {
         return i < c.lv[l + 1].n ? c.cs.cdeg[i] : 0;
     }
     __device__ void post(int64_t nnzc) const {
-        Control *ctrl = c.ctrl;
-        LevelDesc *L = c.lv + l, *N = c.lv + l + 1;
-        // everything read here is loaded before the first decision
-        const int32_t phase = L->phase;
-        const uint32_t flags = ctrl->flags, stall_num = ctrl->stall_num,
-                       stall_den = ctrl->stall_den;
-        const int64_t n = L->n, nc = N->n;
-        if (phase != PH_CONTRACT) return;
-        if (flags & CF_HUBS) {   // rows were left unmerged: stop, the host retries
-            L->phase = PH_STOPPED;
-            ctrl->done = 1;
-            return;
-        }
-        const uint64_t bytes[2] = {(uint64_t)nnzc * 4, (uint64_t)nnzc * 4};
-        void *p[2];
-        const bool ok = arena_alloc_k<2>(ctrl, bytes, p);
-        N->nnz = nnzc;
-        N->adj = (int32_t *)p[0];
-        N->ew = (uint32_t *)p[1];
-        N->maxdeg = 0;   // not tracked below level 0
-        if (!ok) {
-            L->phase = PH_STOPPED;
-            ctrl->done = 1;
-            return;
-        }
-        L->phase = PH_COMPACT;
-        ctrl->nlevels = l + 2;
-        ctrl->last_n = (int32_t)nc;
-        if (stall_num > 0 && (uint64_t)(n - nc) * stall_den < (uint64_t)stall_num * (uint64_t)n) {
-            N->stop = KAPPA_STOP_STALL;
-            N->phase = PH_STOPPED;
-            ctrl->done = 1;
-        }
+        coarse_entries(c, l, nnzc);
     }
 };
 struct CoarseOffW {
@@ -1796,13 +1702,6 @@ __device__ __forceinline__ int32_t *class_list(const ContractScratch &cs, int32_
 // buckets (fill_huge_*) rather than by the dense hub accumulators.
 __device__ __forceinline__ bool huge_row(int64_t nc, int64_t tot) {
     return nc <= HUGE_NC_MAX && tot <= HUGE_ROW_MAX;
-}
-
-// Orders the LDS traffic of one wave (all lanes of the wave call it).
-__device__ __forceinline__ void wave_sync_lds() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
 // Class-list appends through a per-wave LDS buffer: a wave writes its list

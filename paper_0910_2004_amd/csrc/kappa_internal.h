@@ -153,8 +153,10 @@ __device__ __forceinline__ bool cand_better(const Cand &a, const Cand &b, int32_
     if (a.u < 0) return false;
     if (b.u < 0) return true;
     if (((a.num | a.den | b.num | b.den) >> 32) == 0) {
-        // all four below 2^32: the cross products fit 64 bits
-        const uint64_t l = a.num * b.den, r = b.num * a.den;
+        // all four below 2^32: the cross products fit 64 bits, two multiplies
+        // each (a 64-bit product is four, at a quarter of the issue rate)
+        const uint64_t l = (uint64_t)(uint32_t)a.num * (uint32_t)b.den,
+                       r = (uint64_t)(uint32_t)b.num * (uint32_t)a.den;
         if (l != r) return l > r;
     } else {
         uint64_t l_lo = a.num * b.den, l_hi = __umul64hi(a.num, b.den);
@@ -627,7 +629,8 @@ struct Control {
     char *base;
     int32_t stop_n, max_levels;
     uint32_t stall_num, stall_den;
-    int32_t last_n;     // node count of the newest level built (host grid sizing)
+    int32_t last_n;     // node and entry count of the newest level built (host grid sizing)
+    int64_t last_nnz;
 };
 
 // Matching scratch (sized for level 0; reused by every level).
@@ -784,6 +787,118 @@ __device__ __forceinline__ bool arena_alloc_k(Control *c, const uint64_t (&bytes
 #pragma unroll
     for (int i = 0; i < K; ++i) out[i] = base + off[i];
     return true;
+}
+
+template <int G>
+__device__ __forceinline__ Cand group_reduce(Cand cd, int32_t v) {
+    for (int off = G / 2; off > 0; off >>= 1) {
+        Cand o = cand_shfl_xor(cd, off, G);
+        if (cand_better(o, cd, v)) cd = o;
+    }
+    return cd;
+}
+
+__device__ __forceinline__ uint64_t level_seed(const Ctx &c, int l) {
+    return c.seed_direct ? c.seed : mix64(c.seed + (uint64_t)l);
+}
+
+// Orders the LDS traffic of one wave (all lanes of the wave call it).
+__device__ __forceinline__ void wave_sync_lds() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// ===========================================================================
+// Level start (first kernel of a level): stop rules (Section 2 threshold,
+// Section 4), state resets.  Every block takes the same decision from the
+// same inputs; block 0 writes it (the only fields it changes are read as
+// "this level goes on" either way, or end the level for every block).
+// ===========================================================================
+__device__ __forceinline__ bool level_gate(const Ctx &c, int l, bool stop_rules, bool writer) {
+    Control *ctrl = c.ctrl;
+    LevelDesc *L = c.lv + l;
+    if (ctrl->done || ctrl->nlevels != l + 1) return false;
+    const int32_t ph = L->phase;
+    if (ph != PH_IDLE && ph != PH_MATCH) return false;
+    int32_t stop = KAPPA_STOP_NONE;
+    if (stop_rules && L->n <= ctrl->stop_n) stop = KAPPA_STOP_SIZE;
+    else if (stop_rules && l >= ctrl->max_levels) stop = KAPPA_STOP_MAXLEVEL;
+    if (stop != KAPPA_STOP_NONE || !L->mate || !L->cmap) {
+        if (writer) {
+            L->stop = stop;
+            L->phase = PH_STOPPED;
+            ctrl->done = 1;
+        }
+        return false;
+    }
+    if (writer) L->phase = PH_MATCH;
+    return true;
+}
+
+// The coarse level's node arrays (nc nodes; one thread, level l contracting).
+__device__ __forceinline__ void coarse_nodes(const Ctx &c, int l, int64_t nc) {
+    LevelDesc *L = c.lv + l, *N = c.lv + l + 1;
+    if (L->phase != PH_CONTRACT) return;
+    const bool batch = L->gid != nullptr;
+    const uint64_t b4 = (uint64_t)nc * 4;
+    const uint64_t bytes[6] = {b4, (uint64_t)(nc + 1) * 8, b4, b4, batch ? b4 : 0,
+                               batch ? (uint64_t)(c.b.count + 1) * 4 : 0};
+    void *p[6];
+    const bool ok = arena_alloc_k<6>(c.ctrl, bytes, p);
+    N->n = (int32_t)nc;
+    N->vw = (uint32_t *)p[0];
+    N->xadj = (int64_t *)p[1];
+    N->mate = (int32_t *)p[2];
+    N->cmap = (int32_t *)p[3];
+    N->gid = batch ? (int32_t *)p[4] : nullptr;
+    N->noff = batch ? (int32_t *)p[5] : nullptr;
+    N->adj = nullptr;
+    N->ew = nullptr;
+    N->phase = PH_IDLE;
+    N->stop = KAPPA_STOP_NONE;
+    if (!ok) {
+        L->phase = PH_STOPPED;
+        c.ctrl->done = 1;
+    }
+}
+
+// The coarse level's entry arrays (nnzc entries) and the stall rule (one thread).
+__device__ __forceinline__ void coarse_entries(const Ctx &c, int l, int64_t nnzc) {
+    Control *ctrl = c.ctrl;
+    LevelDesc *L = c.lv + l, *N = c.lv + l + 1;
+    // everything read here is loaded before the first decision
+    const int32_t phase = L->phase;
+    const uint32_t flags = ctrl->flags, stall_num = ctrl->stall_num,
+                   stall_den = ctrl->stall_den;
+    const int64_t n = L->n, nc = N->n;
+    if (phase != PH_CONTRACT) return;
+    if (flags & CF_HUBS) {   // rows were left unmerged: stop, the host retries
+        L->phase = PH_STOPPED;
+        ctrl->done = 1;
+        return;
+    }
+    const uint64_t bytes[2] = {(uint64_t)nnzc * 4, (uint64_t)nnzc * 4};
+    void *p[2];
+    const bool ok = arena_alloc_k<2>(ctrl, bytes, p);
+    N->nnz = nnzc;
+    N->adj = (int32_t *)p[0];
+    N->ew = (uint32_t *)p[1];
+    N->maxdeg = 0;   // not tracked below level 0
+    if (!ok) {
+        L->phase = PH_STOPPED;
+        ctrl->done = 1;
+        return;
+    }
+    L->phase = PH_COMPACT;
+    ctrl->nlevels = l + 2;
+    ctrl->last_n = (int32_t)nc;
+    ctrl->last_nnz = nnzc;
+    if (stall_num > 0 && (uint64_t)(n - nc) * stall_den < (uint64_t)stall_num * (uint64_t)n) {
+        N->stop = KAPPA_STOP_STALL;
+        N->phase = PH_STOPPED;
+        ctrl->done = 1;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -949,6 +1064,12 @@ void launch_batch_extract(const BatchExtract *x, int32_t nl, hipStream_t s);
 // table of device arrays).
 void launch_batch_eoff(const int64_t *const *xadj, int32_t nl, const int32_t *noff, int32_t count,
                        int64_t *eoff, hipStream_t s);
+
+// Small levels: from level l on, every level of at most SMALL_N nodes,
+// SMALL_E - n entries and SMALL_DEG entries a row runs in one workgroup, in LDS
+// (a level that does not fit ends the launch before it starts).
+constexpr int SMALL_N = 4096, SMALL_E = 20480, SMALL_DEG = 255;
+void launch_small_levels(const Ctx &c, int l, hipStream_t s);
 
 // Matching only (first kernel: the level gate, which moves an idle level to
 // PH_MATCH unless a stop rule fires; stop_rules = false checks none), e.g.
