@@ -1019,9 +1019,14 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
     // served steps: the host saw the interrupt, so the next launch is the
     // next level's start alone (it ends the step there)
     bool begin_only = false;
-    // power-law graphs hand levels back: small batches keep the levels
-    // launched behind a handed-back one (no-ops then) few
-    if (c.big_blocks > 64) batch = std::min(batch, 2);
+    // Power-law graphs match in many rounds (11 to 34 a level at R-MAT scale
+    // 22), and a level handed back leaves everything launched behind it idle
+    // (a level's 40 launches, 160 us and more, against 35 for a read-back).  So
+    // they get one level a batch, and each plans the rounds the last one took
+    // and a quarter more.
+    const bool hub_graph = c.big_blocks > 64;
+    int plan_rounds = 0;
+    if (hub_graph) batch = bi ? std::min(batch, 2) : 1;
     Control *hc = (Control *)pinned(sizeof(Control));
     SizeHint hint(n0);
     for (;;) {
@@ -1039,7 +1044,8 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
                                            (uint64_t)(int64_t)tail_end,
                                            (uint64_t)(int64_t)c.block_bits,
                                            (uint64_t)(int64_t)ext_level, (uint64_t)ext_round,
-                                           (uint64_t)begin_only, (uint64_t)small_on, deg_bits};
+                                           (uint64_t)begin_only, (uint64_t)small_on, deg_bits,
+                                           (uint64_t)plan_rounds};
         HIPCHK(run_seq(w->c, s, key, [&](hipStream_t q) {
             if (begin_only) {
                 launch_batch_begin(c, launched, q);
@@ -1073,6 +1079,7 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
                 // completes any remainder
                 int rounds = rounds_for(nh, c.t);
                 if (l == 0 && p->rating == KAPPA_INNER_OUTER) rounds = 18;
+                rounds = std::max(rounds, plan_rounds);
                 launch_level(c, l, nh, d0.nnz, n0, rounds, q);
             }
         }));
@@ -1101,7 +1108,8 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
             continue;
         }
         if (hc->done || launched > maxl) break;
-        batch = c.big_blocks > 64 ? 2 : 4;
+        batch = hub_graph ? (bi ? 2 : 1) : 4;
+        if (hub_graph) plan_rounds = std::min(64, hc->last_rounds + hc->last_rounds / 4 + 2);
         if (bi && bi->gbase) {
             // served steps end at the next boundary once a graph stops or the
             // host interrupts: launch two levels at a time (each launched
@@ -1593,7 +1601,9 @@ kappa_status match_once(const kappa_graph *g, int32_t rating, uint64_t level_see
     in->l0.cmap = cm;
     in->l0.phase = PH_IDLE;
     launch_init_levels(c.ctrl, c.lv, 2, in->ctrl, in->l0, s);
-    launch_level_match(c, 0, d.n, d.nnz, 24, false, true, s);
+    // (a launched round that finds nothing left costs two or four launches, a
+    // hand-back for more rounds 40 us)
+    launch_level_match(c, 0, d.n, d.nnz, rating == KAPPA_INNER_OUTER ? 24 : 12, false, true, s);
     LevelDesc *hl = (LevelDesc *)pinned(sizeof(LevelDesc), PIN_LEVELS);
     Control *hc = (Control *)pinned(sizeof(Control));
     for (;;) {

@@ -805,6 +805,7 @@ __global__ void __launch_bounds__(BLOCK) up_entries_k(UpTable T, int32_t k, uint
     __shared__ int last;
     uint64_t cut = 0;
     int li = 0;
+    UpLevel L = T.lv[0];   // level li
     auto flush = [&]() {   // this block's part of level li's cut
         cut = block_sum(cut, sh);
         if (threadIdx.x == 0 && cut)
@@ -818,8 +819,8 @@ __global__ void __launch_bounds__(BLOCK) up_entries_k(UpTable T, int32_t k, uint
         if (l != li) {
             flush();
             li = l;
+            L = T.lv[li];
         }
-        const UpLevel L = T.lv[li];
         const int32_t *const part = L.part;
         DevGraph g;
         g.n = L.n; g.nnz = L.nnz; g.xadj = L.xadj; g.adj = L.adj; g.ew = L.ew; g.vw = L.vw;

@@ -1095,6 +1095,7 @@ __device__ void close_matching(const Ctx &c, LevelDesc *L, bool capped, int grid
         st->handoff = -2;
         L->matched = m;
         L->rounds = used;
+        c.ctrl->last_rounds = used;
         L->grid_rounds = grid_r0 < 0 ? used : min(grid_r0, used);
         if (capped) c.ctrl->flags |= CF_ROUNDS;
         if (defer && !capped) {
@@ -1145,9 +1146,25 @@ __global__ void __launch_bounds__(FINISH_THREADS) finish_k(Ctx c, int l, int r_l
         // power-law graphs): one workgroup would crawl through them, so the
         // level goes back to the host for more grid rounds.  The level stays
         // in PH_MATCH; `done` ends this batch of levels.
+        // The same holds for few nodes with long rows: FINISH_DEG entries take
+        // the workgroup about 30 us a round (100 K entries: 90 us), the grid
+        // 24 us with its four launches.
         const int32_t pend = s_cnt[r0 & 1][0] + s_cnt[r0 & 1][1] + s_cnt[r0 & 1][2];
-        if (F == 0 && st->handoff == -1 && r0 == r_last &&
-            (pend > c.t.finish_max || s_cnt[r0 & 1][2] > c.t.finish_max_big)) {
+        bool back = F == 0 && st->handoff == -1 && r0 == r_last;
+        if (back && pend <= c.t.finish_max && s_cnt[r0 & 1][2] <= c.t.finish_max_big) {
+            int64_t deg = 0;
+            for (int b = 0; b < 3; ++b) {
+                const PList li = plist(c.ms, g.n, r0 & 1, b);
+                for (int i = threadIdx.x; i < min(s_cnt[r0 & 1][b], g.n); i += FINISH_THREADS)
+                    deg += li.d[i];
+            }
+            deg = block_sum(deg, sh);
+            if (threadIdx.x == 0) s_acc[0] = deg;
+            __syncthreads();
+            back = s_acc[0] > FINISH_DEG;
+            __syncthreads();   // s_acc is used again
+        }
+        if (back) {
             if (threadIdx.x == 0) {
                 c.ctrl->ext_level = l;
                 c.ctrl->ext_round = r_last;
@@ -3527,7 +3544,11 @@ template <int R>
 static void launch_later_round(const Ctx &c, int l, int r, const PickGrid &pg, int64_t e,
                                hipStream_t s) {
     const unsigned pick_blocks = pg.b0 + pg.b1 + pg.b2;
-    const unsigned list_blocks = grid_for(e, BLOCK, 2048);
+    // mate: a block's appends are one atomic on the lists' counters, and atomics
+    // on one line take 12 ns each, so a block takes four entries a thread and a
+    // launch at most 512 blocks (R-MAT scale 22: 8.3 ms of mate launches with
+    // 2048 blocks, 5.1 with 512)
+    const unsigned list_blocks = grid_for(e, BLOCK * 4, 512);
     if (c.ms.hub.rec) {
         {
             KAPPA_PROF("prep", s);
@@ -3707,7 +3728,7 @@ static void match_impl(const Ctx &c, int l, int32_t n_hint, int rounds, hipStrea
         pg.b1 = c.big_blocks > 64 ? 2u * c.big_blocks : grid_for(e, BLOCK / WAVE * 8, 128);
         pg.b2 = c.big_blocks > 64 ? (unsigned)c.big_blocks : grid_for(e, 4096, 64);
         const unsigned pick_blocks = pg.b0 + pg.b1 + pg.b2;
-        const unsigned mate_blocks = grid_for(e, BLOCK, 2048);
+        const unsigned mate_blocks = grid_for(e, BLOCK * 4, 512);
         if (r == 1) {
             {
                 KAPPA_PROF("pick_first", s);
