@@ -741,12 +741,12 @@ void carve_scratch(Carve &cv, const DevGraph &g, int rating, bool hubs, Ctx &c,
     // two-phase matcher (c.block_bits set before carving)
     ms.loc = c.block_bits >= 0 ? cv.get<int32_t>(g.n) : nullptr;
     ms.lkey = c.block_bits >= 0 ? cv.get<LocKey>(g.n) : nullptr;
-    ms.hub = HubChunks{nullptr, nullptr, nullptr, 0, nullptr, nullptr};
+    ms.hub = HubChunks{};
     if (chunks) {
         ms.hub.cap = hub_chunk_cap(g.nnz);
         ms.hub.rec = cv.get<int2>(2 * ms.hub.cap);
-        ms.hub.first = cv.get<int32_t>(2 * (int64_t)g.n);
         ms.hub.part = cv.get<Cand>(ms.hub.cap);
+        ms.hub.arrive = cv.get<int32_t>(ms.hub.cap);
         ms.hub.scan = cv.get<int2>(2 * (int64_t)g.n);
         ms.hub.kfirst = cv.get<int32_t>(g.n);
     }
@@ -759,6 +759,7 @@ void fill_scratch(const DevGraph &g, const Ctx &c, hipStream_t s) {
     z.add(c.cs.totals, 4 * 2);
     z.add(c.ms.coop_bar, 2 + ARRIVE_WORDS);
     z.add(c.cs.hg_cnt, 4);
+    z.add(c.ms.hub.arrive, c.ms.hub.cap);
     // the matching state: list counters, round statistics, merge counts
     static_assert(sizeof(MatchState) % 4 == 0, "zeroed as words");
     z.add(c.ms.state, sizeof(MatchState) / 4);

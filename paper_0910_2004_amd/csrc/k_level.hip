@@ -267,19 +267,17 @@ __device__ __forceinline__ uint64_t row_seed(const Ctx &c, const DevGraph &g, in
 constexpr int MK = 8;
 // Where the chunk records of appended bin-2 entries go (rec == nullptr: none;
 // the one-workgroup finisher scans long rows whole).  cnt: the record counter.
-// kfirst (round 1 only): each row's first record is also kept by node.
+// kfirst (round 1 only): each row's first record, kept by node.
 struct HubOut {
     int2 *rec;
-    int32_t *first;
     int32_t *cnt;
     int64_t cap;
     int32_t *kfirst;
 };
-__device__ __forceinline__ HubOut hub_out(const Ctx &c, int32_t n, int par, int32_t *cnt3) {
-    HubOut h{nullptr, nullptr, nullptr, 0, nullptr};
+__device__ __forceinline__ HubOut hub_out(const Ctx &c, int par, int32_t *cnt3) {
+    HubOut h{nullptr, nullptr, 0, nullptr};
     if (!c.ms.hub.rec) return h;
     h.rec = c.ms.hub.rec + (int64_t)par * c.ms.hub.cap;
-    h.first = c.ms.hub.first + (int64_t)par * n;
     h.cnt = cnt3 + 3;
     h.cap = c.ms.hub.cap;
     h.kfirst = c.ms.hub.kfirst;
@@ -296,11 +294,9 @@ __device__ __forceinline__ void hub_emit(const HubOut &h, int32_t p, int32_t v, 
     const int32_t base = atomicAdd(h.cnt, k);
     if ((int64_t)base + k > h.cap) {   // cannot happen: the capacity bounds every level
         atomicOr(&ctrl->flags, (uint32_t)CF_STATE);
-        h.first[p] = -1;
         if (h.kfirst) h.kfirst[v] = -1;
         return;
     }
-    h.first[p] = base;
     if (h.kfirst) h.kfirst[v] = base;
     for (int32_t q = 0; q < k; ++q) h.rec[base + q] = make_int2(p, q);
 }
@@ -339,6 +335,62 @@ __device__ __forceinline__ void block_append_mk(const int bin[MK], const int32_t
     __syncthreads();   // sbase is reused by the next call
 }
 
+// The same of round r for blocks of BLOCK threads, and the entries that rescan
+// in round r + 1 to its scan lists ({node, list position}) or, of bin 2, to chunk
+// records; one scan and one atomic for all five.  sbase: 5 int32 of LDS.
+__device__ __forceinline__ void block_append_rescan(const Ctx &c, int32_t n, int r,
+                                                    const int bin[MK], const bool resc[MK],
+                                                    const int32_t v[MK], const int32_t b[MK],
+                                                    const int32_t d[MK], const PList ol[3],
+                                                    int32_t *cnt, int64_t *sh, int32_t *sbase) {
+    static_assert(BLOCK * MK < 1 << 12, "12 bits a list");
+    constexpr int64_t M = 0xfff;
+    int32_t *const sc = c.ms.state->scnt[(r + 1) & 3];
+    const HubOut ho{c.ms.hub.rec + (int64_t)(r & 1) * c.ms.hub.cap, sc + 3, c.ms.hub.cap, nullptr};
+    int64_t packed = 0;
+#pragma unroll
+    for (int k = 0; k < MK; ++k) {
+        if (bin[k] < 0) continue;
+        packed += (int64_t)1 << (12 * bin[k]);
+        if (resc[k] && bin[k] < 2) packed += (int64_t)1 << (36 + 12 * bin[k]);
+    }
+    int64_t tot;
+    const int64_t pre = block_excl_scan(packed, sh, &tot);
+    if (threadIdx.x < 5) {
+        const int32_t t = (int32_t)((tot >> (12 * threadIdx.x)) & M);
+        int32_t *const at = threadIdx.x < 3 ? &cnt[threadIdx.x] : &sc[threadIdx.x - 3];
+        sbase[threadIdx.x] = t ? atomicAdd(at, t) : 0;
+    }
+    __syncthreads();
+    int32_t p[5];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) p[q] = sbase[q] + (int32_t)((pre >> (12 * q)) & M);
+    int2 *const scan0 = c.ms.hub.scan, *const scan1 = c.ms.hub.scan + n;
+#pragma unroll
+    for (int k = 0; k < MK; ++k) {
+        if (bin[k] < 0) continue;
+        int32_t at;
+        PList o;
+        if (bin[k] == 0) {
+            at = p[0]++;
+            o = ol[0];
+            if (resc[k]) scan0[p[3]++] = make_int2(v[k], at);
+        } else if (bin[k] == 1) {
+            at = p[1]++;
+            o = ol[1];
+            if (resc[k]) scan1[p[4]++] = make_int2(v[k], at);
+        } else {
+            at = p[2]++;
+            o = ol[2];
+            if (resc[k]) hub_emit(ho, at, v[k], d[k], c.ctrl);
+        }
+        o.v[at] = v[k];
+        o.b[at] = b[k];
+        o.d[at] = d[k];
+    }
+    __syncthreads();   // sbase is reused by the next call
+}
+
 // --- phases of the per-round kernels --------------------------------------
 
 // mate = best = -1; nodes of bins 1 and 2 go to the round-1 lists (parity 0).
@@ -352,7 +404,7 @@ __device__ __forceinline__ void init_phase(const Ctx &c, const DevGraph &g, Leve
     const PList ol[3] = {plist(c.ms, g.n, 0, 0), plist(c.ms, g.n, 0, 1), plist(c.ms, g.n, 0, 2)};
     // chunk records only for the grid rounds (a one-workgroup caller scans
     // long rows whole, and its counters have no chunk slot)
-    const HubOut ho = grid ? hub_out(c, g.n, 0, cnt) : HubOut{};
+    const HubOut ho = grid ? hub_out(c, 0, cnt) : HubOut{};
     // pass p, slot k of block b covers entries ((p * MK + k) * nb + b) * blockDim.x + t:
     // small inputs spread over every block first
     const int64_t row = (int64_t)nb * blockDim.x, per_pass = row * MK;
@@ -390,8 +442,7 @@ struct RoundIn {
     int32_t cn[3];
     int32_t nrec;
     const int2 *rec;
-    const int32_t *first;
-    // rounds >= 2 with a preparation launch: the rows to rescan
+    // rounds >= 2 with long rows in chunks: the rows to rescan
     const int2 *scan[2];
     int32_t scn[2];
 };
@@ -407,16 +458,14 @@ __device__ __forceinline__ RoundIn round_inputs(const Ctx &c, const DevGraph &g,
     if (FIRST) ri.cn[0] = g.n;
     ri.nrec = 0;
     ri.rec = nullptr;
-    ri.first = nullptr;
     ri.scan[0] = ri.scan[1] = nullptr;
     ri.scn[0] = ri.scn[1] = 0;
     if (c.ms.hub.rec) {
         // round 1: records of every bin-2 row (the init lists); later rounds:
-        // records and scan lists of the rows the preparation found to rescan
+        // records and scan lists of the rows the last round left to rescan
         const int32_t *sc = FIRST ? cnt3 : c.ms.state->scnt[r & 3];
         ri.nrec = (int32_t)min<int64_t>(sc[3], c.ms.hub.cap);
         ri.rec = c.ms.hub.rec + (int64_t)par * c.ms.hub.cap;
-        ri.first = c.ms.hub.first + (int64_t)par * g.n;
         if (!FIRST) {
             for (int b = 0; b < 2; ++b) {
                 ri.scan[b] = c.ms.hub.scan + (int64_t)b * g.n;
@@ -523,7 +572,7 @@ __device__ __forceinline__ void pick_bin2(const Ctx &c, const DevGraph &g, uint6
     }
 }
 
-// Rounds >= 2 after a preparation: bins 0 and 1 over the rows to rescan
+// Rounds >= 2 with long rows in chunks: bins 0 and 1 over the rows to rescan
 // ({node, list position}); the list's choice field is updated for the mutual
 // check.
 template <int R>
@@ -586,15 +635,35 @@ __device__ __forceinline__ void pick_scan1(const Ctx &c, const DevGraph &g, uint
     }
 }
 
+// A chunk's maximum, read and written past the caches of the block's XCD: the
+// blocks of one row run on any of them.
+__device__ __forceinline__ void part_store(Cand *p, const Cand &cd) {
+    uint64_t *q = (uint64_t *)p;
+    __hip_atomic_store(&q[0], cd.num, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&q[1], cd.den, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&q[2], cd.h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&q[3], (uint64_t)(uint32_t)cd.u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ Cand part_load(const Cand *p) {
+    const uint64_t *q = (const uint64_t *)p;
+    Cand cd;
+    cd.num = __hip_atomic_load(&q[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    cd.den = __hip_atomic_load(&q[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    cd.h = __hip_atomic_load(&q[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    cd.u = (int32_t)(uint32_t)__hip_atomic_load(&q[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return cd;
+}
+
 // bin 2 in the grid rounds: one block per chunk of HUB_CHUNK entries.  A row
 // of one chunk gets its choice at once; longer rows keep one maximum per
 // chunk in hub.part, at the row's round-1 records (hub.kfirst) for the whole
-// level, for hub_reduce_k.  Records exist only for rows that scan this round
-// (round 1: every row; later rounds: the rows whose choice was matched away,
-// found by prep_k).  In a later round a chunk whose kept maximum is still
-// free, or that had no free neighbour, keeps it without a scan: the free
-// set only shrinks, so that maximum is still the chunk's best free
-// neighbour.  r: the round (statistics).
+// level, and the row's last block to arrive (hub.arrive) takes their best (a
+// launch for that alone was 3 to 5 us a round).  Records exist only for rows
+// that scan this round (round 1: every row; later rounds: the rows whose choice
+// was matched away, found by the last round's mutual check).  In a later round
+// a chunk whose kept maximum is still free, or that had no free neighbour, keeps
+// it without a scan: the free set only shrinks, so that maximum is still the
+// chunk's best free neighbour.  r: the round (statistics).
 template <int R, bool FIRST>
 __device__ __forceinline__ void pick_bin2_chunks(const Ctx &c, const DevGraph &g, uint64_t seed,
                                                  const RoundIn &ri, unsigned bid, unsigned nb,
@@ -605,6 +674,32 @@ __device__ __forceinline__ void pick_bin2_chunks(const Ctx &c, const DevGraph &g
     const int2 *nrec = c.ms.nrec;
     const uint32_t *out = c.ms.out;
     int64_t scanned = 0;   // entries scanned by this block (thread 0)
+    __shared__ int last;
+    // A chunk of row v (list position p) is done: its block, after thread 0's
+    // store of the maximum has completed (write-through, so the wait is for the
+    // memory all XCDs share), counts; the last one reduces.  Block-uniform.
+    auto row_arrive = [&](int32_t p, int32_t v, int32_t kf, int32_t kc) {
+        if (threadIdx.x == 0) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            int32_t *const a = &c.ms.hub.arrive[kf];
+            last = __hip_atomic_fetch_add(a, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kc - 1;
+            if (last) __hip_atomic_store(a, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (last && threadIdx.x < WAVE) {
+            Cand cd = cand_none();
+            for (int32_t t = threadIdx.x; t < kc; t += WAVE) {
+                const Cand o = part_load(&c.ms.hub.part[kf + t]);
+                if (cand_better(o, cd, v)) cd = o;
+            }
+            cd = group_reduce<WAVE>(cd, v);
+            if (threadIdx.x == 0) {
+                best[v] = cd.u;
+                ri.in[2].b[p] = cd.u;
+            }
+        }
+        __syncthreads();   // last is written again
+    };
     for (int64_t q = bid; q < ri.nrec; q += nb) {   // block-uniform
         const int2 rc = ri.rec[q];
         if ((uint32_t)rc.x >= (uint32_t)ri.cn[2]) continue;   // valid records never
@@ -618,8 +713,11 @@ __device__ __forceinline__ void pick_bin2_chunks(const Ctx &c, const DevGraph &g
             continue;
         }
         if (!FIRST && kc > 1) {
-            const int32_t ku = c.ms.hub.part[kf + rc.y].u;
-            if (ku < 0 || nrec[ku].y < 0) continue;
+            const int32_t ku = c.ms.hub.part[kf + rc.y].u;   // (of an earlier launch)
+            if (ku < 0 || nrec[ku].y < 0) {
+                row_arrive(rc.x, v, kf, kc);
+                continue;
+            }
         }
         const int64_t j0 = rb + (int64_t)rc.y * HUB_CHUNK;
         const int64_t j1 = min(re, j0 + HUB_CHUNK);
@@ -659,13 +757,12 @@ __device__ __forceinline__ void pick_bin2_chunks(const Ctx &c, const DevGraph &g
             if (cand_better(e, cd, v)) cd = e;
         }
         cd = block_reduce_cand(cd, v, sh);
-        if (threadIdx.x == 0) {
-            if (kc == 1) {
-                best[v] = cd.u;
-                ri.in[2].b[rc.x] = cd.u;
-            } else {
-                c.ms.hub.part[kf + rc.y] = cd;
-            }
+        if (kc > 1) {
+            if (threadIdx.x == 0) part_store(&c.ms.hub.part[kf + rc.y], cd);
+            row_arrive(rc.x, v, kf, kc);
+        } else if (threadIdx.x == 0) {
+            best[v] = cd.u;
+            ri.in[2].b[rc.x] = cd.u;
         }
     }
     if (!FIRST && c.rescan_stats && threadIdx.x == 0 && scanned > 0) {
@@ -679,7 +776,12 @@ __device__ __forceinline__ void pick_bin2_chunks(const Ctx &c, const DevGraph &g
 // record), survivors appended to the output lists (counters ocnt[3]).
 // Round 1 also writes every node's record {attribute, mate}.  A thread's MK
 // entries are loaded first, then their partners' choices, then stored.
-template <int R, bool FIRST>
+// HUBS (long rows in chunks): a survivor whose choice b was matched in this
+// round (b's own choice points back at b) rescans in the next one; it goes to
+// that round's scan list with its list position, a bin-2 row to chunk records.
+// One look further here replaces a pass over the lists of its own (prep: 5 us a
+// round at scale 14, 26 at scale 22).
+template <int R, bool FIRST, bool HUBS = false>
 __device__ __forceinline__ void mate_phase(const Ctx &c, const DevGraph &g, LevelDesc *L, int r,
                                            const RoundIn &ri, int32_t *ocnt, unsigned bid,
                                            unsigned nb, int64_t *sh, int32_t *sbase) {
@@ -694,6 +796,7 @@ __device__ __forceinline__ void mate_phase(const Ctx &c, const DevGraph &g, Leve
     const PList ol[3] = {plist(c.ms, n, opar, 0), plist(c.ms, n, opar, 1), plist(c.ms, n, opar, 2)};
     int64_t point = 0, degs = 0, pairs = 0;
     int64_t scanned = 0, sdeg = 0;   // later rounds without chunked rows: every entry rescanned
+    int64_t rrows = 0, rdeg = 0;     // HUBS: the rows round r + 1 rescans
     bool bad = false;
     // pass p, slot k of block b covers entries ((p * MK + k) * nb + b) * blockDim.x + t
     const int64_t row = (int64_t)nb * blockDim.x, per_pass = row * MK;
@@ -740,6 +843,14 @@ __device__ __forceinline__ void mate_phase(const Ctx &c, const DevGraph &g, Leve
             }
             bq[k] = bb[k] >= 0 ? best[bb[k]] : -2;
         }
+        bool resc[MK];
+        if (HUBS) {
+#pragma unroll
+            for (int k = 0; k < MK; ++k) {
+                const bool on = bb[k] >= 0 && bq[k] != vv[k] && (uint32_t)bq[k] < (uint32_t)n;
+                resc[k] = on && best[bq[k]] == bb[k];
+            }
+        }
         // 3. decide and store
 #pragma unroll
         for (int k = 0; k < MK; ++k) {
@@ -767,7 +878,17 @@ __device__ __forceinline__ void mate_phase(const Ctx &c, const DevGraph &g, Leve
                 nrec[v].y = m;
             }
         }
-        block_append_mk(bin, vv, bb, dd, ol, ocnt, sh, sbase);
+        if (HUBS) {
+            block_append_rescan(c, g.n, r, bin, resc, vv, bb, dd, ol, ocnt, sh, sbase);
+#pragma unroll
+            for (int k = 0; k < MK; ++k) {
+                if (bin[k] < 0 || !resc[k]) continue;
+                ++rrows;
+                if (bin[k] < 2) rdeg += dd[k];   // chunked rows: the pick counts what it scans
+            }
+        } else {
+            block_append_mk(bin, vv, bb, dd, ol, ocnt, sh, sbase);
+        }
     }
     if (__ballot(bad) && lane_id() == 0) atomicOr(&c.ctrl->flags, (uint32_t)CF_STATE);
     // with the rows this round's pick scanned, where it scans every pending
@@ -790,6 +911,15 @@ __device__ __forceinline__ void mate_phase(const Ctx &c, const DevGraph &g, Leve
     if (!FIRST && !c.ms.hub.rec && threadIdx.x == 0 && sums[3] > 0) {
         atomicAdd((unsigned long long *)&st->sstat[ri_][3][sd], (unsigned long long)sums[3]);
         atomicAdd((unsigned long long *)&st->sstat[ri_][4][sd], (unsigned long long)sums[4]);
+    }
+    if (HUBS && c.rescan_stats) {
+        int64_t none = 0;
+        block_sum3(rrows, rdeg, none, sh);
+        if (threadIdx.x == 0 && rrows > 0) {
+            const int rn = r < STAT_ROUNDS ? r : STAT_ROUNDS - 1;
+            atomicAdd((unsigned long long *)&st->sstat[rn][3][sd], (unsigned long long)rrows);
+            atomicAdd((unsigned long long *)&st->sstat[rn][4][sd], (unsigned long long)rdeg);
+        }
     }
 }
 
@@ -825,7 +955,7 @@ struct PickGrid {
     unsigned b0, b1, b2;  // blocks per bin
 };
 
-// SCAN (rounds >= 2, long rows in chunks): the rows prep_k found to rescan.
+// SCAN (rounds >= 2, long rows in chunks): the rows the last round left to rescan.
 template <int R, bool FIRST, int F = 0, bool SCAN = false>
 __global__ void __launch_bounds__(BLOCK) pick_k(Ctx c, int l, int r, PickGrid pg) {
     __shared__ Cand sh[BLOCK / WAVE];
@@ -866,143 +996,11 @@ __global__ void __launch_bounds__(BLOCK) pick_k(Ctx c, int l, int r, PickGrid pg
         pick_bin2<R, FIRST, BLOCK, F>(c, g, seed, ri, bid, pg.b2, sh);
 }
 
-// Preparation of round r >= 2 (long rows in chunks): every pending entry
-// whose choice was matched away in round r - 1 must rescan its row.  Rows of
-// bins 0 and 1 go to the scan lists ({node, list position}); bin-2 rows get
-// their chunk records (first = the row's first record, -1 for a row that
-// keeps its choice).  Also applies the hand-over tests of the round (nothing
-// pending, or few enough for the finisher).  A thread's MK entries are loaded
-// together.
-__global__ void __launch_bounds__(BLOCK) prep_k(Ctx c, int l, int r) {
-    __shared__ int64_t sh[5 * (BLOCK / WAVE) + 1];
-    __shared__ int32_t sbase[2];
-    DevGraph g;
-    LevelDesc *L = c.lv + l;
-    if (!load_level(L, PH_MATCH, g)) return;
-    MatchState *st = c.ms.state;
-    if (st->handoff != -1 || !c.ms.hub.rec) return;
-    const RoundIn ri = round_inputs<false>(c, g, r, st->cnt[(r - 1) & 3]);
-    const int32_t c0 = ri.cn[0], c1 = ri.cn[1];
-    const int64_t total = (int64_t)c0 + c1 + ri.cn[2];
-    if (total == 0 || total <= c.t.tail_max) {
-        if (blockIdx.x == 0 && threadIdx.x == 0)
-            atomicCAS(&st->handoff, -1, total == 0 ? -2 : r - 1);
-        return;
-    }
-    int32_t *sc = st->scnt[r & 3];
-    int2 *const scan0 = c.ms.hub.scan, *const scan1 = c.ms.hub.scan + g.n;
-    const int par = (r - 1) & 1;
-    const HubOut ho{c.ms.hub.rec + (int64_t)par * c.ms.hub.cap,
-                    c.ms.hub.first + (int64_t)par * g.n, sc + 3, c.ms.hub.cap, nullptr};
-    const int2 *nrec = c.ms.nrec;
-    const int64_t row = (int64_t)gridDim.x * blockDim.x, per_pass = row * MK;
-    int64_t rrows = 0, rdeg = 0;   // the round's rescanning rows and their degrees
-    for (int64_t base = 0; base < total; base += per_pass) {   // block-uniform
-        const int64_t first = base + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-        int32_t vv[MK], bb[MK], dd[MK], jj[MK], bin[MK];
-        bool resc[MK];
-#pragma unroll
-        for (int k = 0; k < MK; ++k) {
-            const int64_t i = first + (int64_t)k * row;
-            bin[k] = -1;
-            vv[k] = bb[k] = -1;
-            dd[k] = 0;
-            jj[k] = 0;
-            if (i >= total) continue;
-            PList src;
-            if (i < c0) { src = ri.in[0]; jj[k] = (int32_t)i; bin[k] = 0; }
-            else if (i < (int64_t)c0 + c1) { src = ri.in[1]; jj[k] = (int32_t)(i - c0); bin[k] = 1; }
-            else { src = ri.in[2]; jj[k] = (int32_t)(i - c0 - c1); bin[k] = 2; }
-            vv[k] = src.v[jj[k]];
-            bb[k] = src.b[jj[k]];
-            dd[k] = src.d[jj[k]];
-        }
-#pragma unroll
-        for (int k = 0; k < MK; ++k) {
-            const bool live = bin[k] >= 0 && (uint32_t)vv[k] < (uint32_t)g.n;
-            resc[k] = live && !keeps_choice(bb[k], g.n, nrec);
-            if (bin[k] >= 0 && !live) bin[k] = -1;   // valid lists never
-            if (resc[k]) {
-                ++rrows;
-                if (bin[k] < 2) rdeg += dd[k];   // chunked rows: the pick counts what it scans
-            }
-        }
-        // rows of bins 0 and 1 that rescan: block-aggregated append
-        int64_t packed = 0;
-#pragma unroll
-        for (int k = 0; k < MK; ++k)
-            if (resc[k] && bin[k] < 2) packed += (int64_t)1 << (21 * bin[k]);
-        int64_t tot;
-        const int64_t pre = block_excl_scan(packed, sh, &tot);
-        if (threadIdx.x < 2) {
-            const int32_t t = (int32_t)((tot >> (21 * threadIdx.x)) & 0x1fffff);
-            sbase[threadIdx.x] = t ? atomicAdd(&sc[threadIdx.x], t) : 0;
-        }
-        __syncthreads();
-        int32_t p0 = sbase[0] + (int32_t)(pre & 0x1fffff);
-        int32_t p1 = sbase[1] + (int32_t)((pre >> 21) & 0x1fffff);
-#pragma unroll
-        for (int k = 0; k < MK; ++k) {
-            if (bin[k] == 2) {
-                if (resc[k]) hub_emit(ho, jj[k], vv[k], dd[k], c.ctrl);
-                else ho.first[jj[k]] = -1;
-            } else if (resc[k]) {
-                if (bin[k] == 0) scan0[p0++] = make_int2(vv[k], jj[k]);
-                else scan1[p1++] = make_int2(vv[k], jj[k]);
-            }
-        }
-        __syncthreads();   // sbase is reused by the next pass
-    }
-    if (!c.rescan_stats) return;
-    int64_t none = 0;
-    block_sum3(rrows, rdeg, none, sh);
-    if (threadIdx.x == 0 && rrows > 0) {
-        const int ri_ = r - 1 < STAT_ROUNDS ? r - 1 : STAT_ROUNDS - 1, sd = shard_of_block();
-        atomicAdd((unsigned long long *)&st->sstat[ri_][3][sd], (unsigned long long)rrows);
-        atomicAdd((unsigned long long *)&st->sstat[ri_][4][sd], (unsigned long long)rdeg);
-    }
-}
-
-// The choices of bin-2 rows of more than one chunk: the best of their
-// chunks' maxima (one wave per row).  Runs between the pick and the mate
-// launches of a grid round, under the same gates.
-template <bool FIRST>
-__global__ void __launch_bounds__(BLOCK) hub_reduce_k(Ctx c, int l, int r) {
-    DevGraph g;
-    LevelDesc *L = c.lv + l;
-    if (!load_level(L, PH_MATCH, g)) return;
-    MatchState *st = c.ms.state;
-    if (st->handoff != -1 || !c.ms.hub.rec) return;
-    const RoundIn ri = round_inputs<FIRST>(c, g, r, st->cnt[FIRST ? 0 : (r - 1) & 3]);
-    int32_t *best = c.ms.best;
-    const int64_t gi = (int64_t)blockIdx.x * (BLOCK / WAVE) + threadIdx.x / WAVE;
-    const int64_t gs = (int64_t)gridDim.x * (BLOCK / WAVE);
-    for (int64_t i = gi; i < ri.cn[2]; i += gs) {   // wave-uniform
-        const int32_t f = ri.first[i];   // -1: the row keeps its choice (prep_k)
-        if (f < 0) continue;
-        const int32_t v = ri.in[2].v[i];
-        if ((uint32_t)v >= (uint32_t)g.n) continue;   // flagged by the pick
-        const int32_t k = hub_chunks_of(g.xadj[v + 1] - g.xadj[v]);
-        if (k <= 1) continue;
-        const int32_t kf = c.ms.hub.kfirst[v];   // the row's chunk maxima for the level
-        if (kf < 0 || (int64_t)kf + k > c.ms.hub.cap) continue;   // flagged by the pick
-        Cand cd = cand_none();
-        for (int32_t q = lane_id(); q < k; q += WAVE) {
-            const Cand o = c.ms.hub.part[kf + q];
-            if (cand_better(o, cd, v)) cd = o;
-        }
-        cd = group_reduce<WAVE>(cd, v);
-        if (lane_id() == 0) {
-            best[v] = cd.u;
-            ri.in[2].b[i] = cd.u;
-        }
-    }
-}
-
-template <int R, bool FIRST>
+// HUBS: long rows in chunks; the rows round r + 1 rescans go to its lists.
+template <int R, bool FIRST, bool HUBS = false>
 __global__ void __launch_bounds__(BLOCK) mate_k(Ctx c, int l, int r) {
     __shared__ int64_t sh[5 * (BLOCK / WAVE) + 1];
-    __shared__ int32_t sbase[3];
+    __shared__ int32_t sbase[5];
     DevGraph g;
     LevelDesc *L = c.lv + l;
     if (!load_level(L, PH_MATCH, g)) return;
@@ -1015,7 +1013,7 @@ __global__ void __launch_bounds__(BLOCK) mate_k(Ctx c, int l, int r) {
         st->cnt[(r + 2) & 3][threadIdx.x] = 0;
         st->scnt[(r + 2) & 3][threadIdx.x] = 0;
     }
-    mate_phase<R, FIRST>(c, g, L, r, ri, st->cnt[r & 3], blockIdx.x, gridDim.x, sh, sbase);
+    mate_phase<R, FIRST, HUBS>(c, g, L, r, ri, st->cnt[r & 3], blockIdx.x, gridDim.x, sh, sbase);
 }
 
 // Rounds r0+1, r0+2, ... of level L in one workgroup of NT threads, with
@@ -1173,6 +1171,9 @@ __global__ void __launch_bounds__(FINISH_THREADS) finish_k(Ctx c, int l, int r_l
             }
             return;
         }
+        // (the rescans counted for a grid round that did not come)
+        if (F == 0 && c.rescan_stats && c.ms.hub.rec && r0 < STAT_ROUNDS - 1 && threadIdx.x < 2 * NSHARD)
+            st->sstat[r0][3 + threadIdx.x / NSHARD][threadIdx.x % NSHARD] = 0;
         capped = wg_rounds<R, FINISH_THREADS, F>(c, g, L, seed, r0, s_cnt, shc, sh, sbase);
     }
     // r0 = -2: the round kernels found nothing left, so they ran every round
@@ -3528,17 +3529,8 @@ void launch_union_build(const UnionSrc *src, int32_t count, const int64_t *noff,
 // Host side
 // ===========================================================================
 
-// Launched only when the long rows of the level are scanned in chunks.
-template <bool FIRST>
-static void launch_hub_reduce(const Ctx &c, int l, int r, hipStream_t s) {
-    if (!c.ms.hub.rec) return;
-    KAPPA_PROF("hub_reduce", s);
-    hipLaunchKernelGGL(hub_reduce_k<FIRST>, dim3(256), dim3(BLOCK), 0, s, c, l, r);
-}
-
-// Grid round r >= 2 (e: estimate of the pending entries).  With long rows in
-// chunks: preparation (the rows that rescan), pick over those, reduction of
-// the chunked rows, mutual check; otherwise pick over the pending lists and
+// Grid round r >= 2 (e: estimate of the pending entries): pick, over the rows to
+// rescan where long rows are in chunks and over the pending lists otherwise, and
 // the mutual check.
 template <int R>
 static void launch_later_round(const Ctx &c, int l, int r, const PickGrid &pg, int64_t e,
@@ -3549,24 +3541,15 @@ static void launch_later_round(const Ctx &c, int l, int r, const PickGrid &pg, i
     // launch at most 512 blocks (R-MAT scale 22: 8.3 ms of mate launches with
     // 2048 blocks, 5.1 with 512)
     const unsigned list_blocks = grid_for(e, BLOCK * 4, 512);
-    if (c.ms.hub.rec) {
-        {
-            KAPPA_PROF("prep", s);
-            hipLaunchKernelGGL(prep_k, dim3(grid_for(e, BLOCK * MK, 2048)), dim3(BLOCK), 0, s, c,
-                               l, r);
-        }
-        {
-            KAPPA_PROF("pick", s);
-            hipLaunchKernelGGL((pick_k<R, false, 0, true>), dim3(pick_blocks), dim3(BLOCK), 0, s,
-                               c, l, r, pg);
-        }
-        launch_hub_reduce<false>(c, l, r, s);
-    } else {
+    const bool hubs = c.ms.hub.rec != nullptr;
+    {
         KAPPA_PROF("pick", s);
-        hipLaunchKernelGGL((pick_k<R, false>), dim3(pick_blocks), dim3(BLOCK), 0, s, c, l, r, pg);
+        const auto k = hubs ? pick_k<R, false, 0, true> : pick_k<R, false, 0, false>;
+        hipLaunchKernelGGL(k, dim3(pick_blocks), dim3(BLOCK), 0, s, c, l, r, pg);
     }
     KAPPA_PROF("mate", s);
-    hipLaunchKernelGGL((mate_k<R, false>), dim3(list_blocks), dim3(BLOCK), 0, s, c, l, r);
+    const auto k = hubs ? mate_k<R, false, true> : mate_k<R, false, false>;
+    hipLaunchKernelGGL(k, dim3(list_blocks), dim3(BLOCK), 0, s, c, l, r);
 }
 
 // ---------------------------------------------------------------------------
@@ -3735,9 +3718,9 @@ static void match_impl(const Ctx &c, int l, int32_t n_hint, int rounds, hipStrea
                 hipLaunchKernelGGL((pick_k<R, true>), dim3(pick_blocks), dim3(BLOCK), 0, s, c, l, r,
                                    pg);
             }
-            launch_hub_reduce<true>(c, l, r, s);
             KAPPA_PROF("mate_first", s);
-            hipLaunchKernelGGL((mate_k<R, true>), dim3(mate_blocks), dim3(BLOCK), 0, s, c, l, r);
+            const auto k = c.ms.hub.rec ? mate_k<R, true, true> : mate_k<R, true, false>;
+            hipLaunchKernelGGL(k, dim3(mate_blocks), dim3(BLOCK), 0, s, c, l, r);
         } else {
             launch_later_round<R>(c, l, r, pg, e, s);
         }

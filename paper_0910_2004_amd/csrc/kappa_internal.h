@@ -656,21 +656,20 @@ struct LocKey {
 };
 // Rows above BIN_MID_MAX entries are scanned in chunks of HUB_CHUNK entries,
 // one block per chunk, so that a round's latency does not grow with the
-// longest row; the chunks' partial maxima are reduced per row by a separate
-// launch before the mutual check.
+// longest row; a row's last block reduces the chunks' partial maxima.
 constexpr int HUB_CHUNK = 2048;
 // Chunk records of a level's bin-2 lists, per list parity: at most one per
 // HUB_CHUNK entries of a row plus one per row, and every bin-2 row has more
 // than BIN_MID_MAX entries, so nnz / 512 + 64 records always suffice.
 inline int64_t hub_chunk_cap(int64_t nnz) { return nnz / 512 + 64; }
+static_assert(sizeof(Cand) == 32, "a chunk's maximum is four words");
 struct HubChunks {
     int2 *rec;       // 2 * cap: per parity, {position in the bin-2 list, chunk index}
-    int32_t *first;  // 2 * n: per parity and bin-2 list position, the row's first record
-                     // (-1: the row keeps its choice this round)
-    Cand *part;      // cap: the chunks' maxima of the current round
+    Cand *part;      // cap: the chunks' maxima
+    int32_t *arrive; // cap: by a row's first record, its chunks done in a round (zero between)
     int64_t cap;
     int2 *scan;      // 2 * n: per bin 0 / 1, {node, list position} of the rows a round
-                     // rescans (written by the round's preparation)
+                     // rescans (written by the last round's mutual check)
     int32_t *kfirst; // n: per node of a chunked row, its first record of round 1, where
                      // part keeps the row's chunk maxima for the rest of the level
 };
@@ -908,7 +907,7 @@ __device__ __forceinline__ void coarse_entries(const Ctx &c, int l, int64_t nnzc
 // ---------------------------------------------------------------------------
 // k_graph.hip
 // Up to ZERO_MAX ranges of 4-byte words zeroed by one launch.
-constexpr int ZERO_MAX = 8;
+constexpr int ZERO_MAX = 10;
 struct ZeroRanges {
     uint32_t *p[ZERO_MAX];
     int64_t words[ZERO_MAX];
