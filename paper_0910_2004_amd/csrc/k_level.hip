@@ -1749,7 +1749,13 @@ __device__ __forceinline__ void wbuf_add(bool pred, int32_t val, int32_t *buf, i
 }
 
 // --- 2a. small rows: 16 lanes per row, rank sort; every coarse row passes
-//         here (empty rows get degree 0, bigger rows go to the class lists) --
+//         here (empty rows get degree 0, bigger rows go to the class lists).
+//         One rank over all entries and a look at the neighbour took the place
+//         of a search for the first occurrence and a rank among those: level 0
+//         of a random geometric graph of 2^20 nodes, 8.4 M entries, 184 ->
+//         151 us.  What is left is lines, not instructions: with ids in no
+//         order the partner's row, the gathers of cmap and the staged row are
+//         most of a gigabyte of 128-byte lines --
 // The contraction phases below are written for `nb` blocks of NT threads
 // (block `bid`): the kernels run them over their grid; the tail kernel runs
 // them in one workgroup.
@@ -1758,9 +1764,8 @@ __device__ __forceinline__ void wbuf_add(bool pred, int32_t val, int32_t *buf, i
 template <int NT, bool BIG = true, bool BUF = false>
 __device__ __forceinline__ void fill_small_body(const Ctx &c, int l, unsigned bid, unsigned nb) {
     constexpr int ROWS = NT / ROW_SMALL_G;
-    __shared__ __align__(16) uint32_t sk[ROWS][SM_CAP];   // renamed entries
-    __shared__ __align__(16) uint32_t sr[ROWS][SM_CAP];   // first occurrences only (others INVALID_KEY)
-    __shared__ uint32_t sw[ROWS][SM_CAP];   // weights; a first occurrence collects its duplicates'
+    __shared__ __align__(16) uint32_t sk[ROWS][SM_CAP];   // renamed entries; then in order
+    __shared__ uint32_t sw[ROWS][SM_CAP];                 // their weights in order
     __shared__ int32_t wb[BUF ? NT / WAVE : 1][4][BUF ? WBUF_CAP : 1];
     int wn[4] = {0, 0, 0, 0};
     DevGraph g;
@@ -1804,62 +1809,84 @@ __device__ __forceinline__ void fill_small_body(const Ctx &c, int l, unsigned bi
             wave_append(sub == 0 && cls == 4, x, lists4, &c.cs.row_cnt[4]);
         }
         const int tot = cls == 0 ? (int)r.tot : 0;
-        {
-            constexpr int U = (SM_CAP + ROW_SMALL_G - 1) / ROW_SMALL_G;   // entries per lane
-            uint32_t kk[U], ww[U];
+        constexpr int U = (SM_CAP + ROW_SMALL_G - 1) / ROW_SMALL_G;   // entries per lane
+        uint32_t kk[U], ww[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = sub + u * ROW_SMALL_G;
-                kk[u] = INVALID_KEY;
-                ww[u] = 0;
-                if (t < tot) row_entry(g, cmap, r, t, kk[u], ww[u]);
-            }
+        for (int u = 0; u < U; ++u) {
+            const int t = sub + u * ROW_SMALL_G;
+            kk[u] = INVALID_KEY;
+            ww[u] = 0;
+            if (t < tot) row_entry(g, cmap, r, t, kk[u], ww[u]);
+        }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = sub + u * ROW_SMALL_G;
-                if (t < tot) {
-                    sk[grp][t] = kk[u];
-                    sw[grp][t] = ww[u];
-                }
-            }
+        for (int u = 0; u < U; ++u) {   // whole 16-byte reads: INVALID_KEY behind the row
+            const int t = sub + u * ROW_SMALL_G;
+            if (t < ((tot + 3) & ~3)) sk[grp][t] = kk[u];
         }
         wave_sync_lds();
-        // the first occurrence of a key leads; a later one adds its weight
-        // to it (only leaders receive, only non-leaders send)
-        // (keys read four at a time; slots past the row are masked)
-        for (int t = sub; t < tot; t += ROW_SMALL_G) {
-            const uint32_t k = sk[grp][t];
-            int first = -1;   // the first earlier occurrence of k
-            if (k != INVALID_KEY) {
-                for (int q0 = 0; q0 < t; q0 += 4) {
-                    const uint4 x = *reinterpret_cast<const uint4 *>(&sk[grp][q0]);
-                    if (x.x == k) { first = q0; break; }
-                    if (q0 + 1 < t && x.y == k) { first = q0 + 1; break; }
-                    if (q0 + 2 < t && x.z == k) { first = q0 + 2; break; }
-                    if (q0 + 3 < t && x.w == k) { first = q0 + 3; break; }
-                }
+        // An entry's place in the sorted row: the smaller keys and the equal ones
+        // before it, keys read four at a time.  Whole chunks lie before or
+        // behind a slot's entries, where one bound serves (x < k + 1, x < k);
+        // only the slot's own chunks compare positions.
+        int rank[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            rank[u] = -1;
+            const int t = sub + u * ROW_SMALL_G;
+            const uint32_t k = kk[u];
+            if (t >= tot || k == INVALID_KEY) continue;
+            int n = 0, q0 = 0;
+            for (; q0 < u * ROW_SMALL_G; q0 += 4) {
+                const uint4 x = *reinterpret_cast<const uint4 *>(&sk[grp][q0]);
+                n += (x.x <= k) + (x.y <= k) + (x.z <= k) + (x.w <= k);
             }
-            const bool lead = k != INVALID_KEY && first < 0;
-            sr[grp][t] = lead ? k : INVALID_KEY;
-            if (first >= 0) atomicAdd(&sw[grp][first], sw[grp][t]);
+            for (; q0 < min(tot, (u + 1) * ROW_SMALL_G); q0 += 4) {
+                const uint4 x = *reinterpret_cast<const uint4 *>(&sk[grp][q0]);
+                n += (x.x < k + (q0 < t)) + (x.y < k + (q0 + 1 < t)) + (x.z < k + (q0 + 2 < t)) +
+                     (x.w < k + (q0 + 3 < t));
+            }
+            for (; q0 < tot; q0 += 4) {
+                const uint4 x = *reinterpret_cast<const uint4 *>(&sk[grp][q0]);
+                n += (x.x < k) + (x.y < k) + (x.z < k) + (x.w < k);
+            }
+            rank[u] = n;
         }
         wave_sync_lds();
+        const int gb = (lane_id() / ROW_SMALL_G) * ROW_SMALL_G;   // the group's lanes
+        int nv = 0;   // entries with a key
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u && !__ballot(u * ROW_SMALL_G < tot)) break;
+            nv += (int)__popcll((__ballot(rank[u] >= 0) >> gb) & ((1u << ROW_SMALL_G) - 1));
+            if (rank[u] < 0) continue;
+            sk[grp][rank[u]] = kk[u];
+            sw[grp][rank[u]] = ww[u];
+        }
+        wave_sync_lds();
+        // the first of each run of equal keys takes the run's weight
         int nl = 0;
-        for (int t = sub; t < tot; t += ROW_SMALL_G) {
-            const uint32_t k = sr[grp][t];
-            if (k == INVALID_KEY) continue;
-            int rank = 0;   // distinct keys below k
-            for (int q0 = 0; q0 < tot; q0 += 4) {
-                const uint4 x = *reinterpret_cast<const uint4 *>(&sr[grp][q0]);
-                rank += (x.x < k ? 1 : 0) + (q0 + 1 < tot && x.y < k ? 1 : 0) +
-                        (q0 + 2 < tot && x.z < k ? 1 : 0) + (q0 + 3 < tot && x.w < k ? 1 : 0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u && !__ballot(u * ROW_SMALL_G < nv)) break;
+            const int t = sub + u * ROW_SMALL_G;
+            uint32_t k = 0, w = 0;
+            bool lead = false;
+            if (t < nv) {
+                k = sk[grp][t];
+                lead = t == 0 || sk[grp][t - 1] != k;
+                if (lead) {
+                    w = sw[grp][t];
+                    for (int z = t + 1; z < nv && sk[grp][z] == k; ++z) w += sw[grp][z];
+                }
             }
-            int64_t at = staged_at(r, rank);
-            c.cs.tmp_adj[at] = (int32_t)k;
-            c.cs.tmp_ew[at] = sw[grp][t];
-            ++nl;
+            const uint32_t m = (uint32_t)((__ballot(lead) >> gb) & ((1u << ROW_SMALL_G) - 1));
+            if (lead) {
+                const int64_t at = staged_at(r, nl + __popc(m & ((1u << sub) - 1)));
+                c.cs.tmp_adj[at] = (int32_t)k;
+                c.cs.tmp_ew[at] = w;
+            }
+            nl += __popc(m);
         }
-        for (int o = ROW_SMALL_G / 2; o > 0; o >>= 1) nl += __shfl_xor(nl, o, ROW_SMALL_G);
         if (live && sub == 0 && cls <= 0) c.cs.cdeg[x] = nl;
         wave_sync_lds();
     }

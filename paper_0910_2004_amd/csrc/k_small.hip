@@ -168,8 +168,8 @@ __device__ __forceinline__ void small_mate(SmallLds &s, const uint16_t *list, in
 // Row [a, a + len) of the staged entries (len even, at most G * MU) merged in
 // place by G lanes.  An entry's place in the sorted row is the number of
 // smaller keys and of equal ones before it, counted two 16-bit keys an
-// instruction; at most four entries have one key (two nodes, two neighbours),
-// so the first of them adds up the next three.  Returns the distinct keys.
+// instruction; the first of a run of equal keys (up to four: two nodes, two
+// neighbours) adds up the run.  Returns the distinct keys.
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 template <int G, int MU>
 __device__ __forceinline__ int small_merge(SmallLds &s, int a, int len, int sub) {
@@ -235,11 +235,8 @@ __device__ __forceinline__ int small_merge(SmallLds &s, int a, int len, int sub)
             key[q] = k[t];
             wt[q] = w[t];
             lead = t == 0 || k[t - 1] != key[q];
-            if (lead) {
-#pragma unroll
-                for (int z = 1; z < 4; ++z)
-                    if (t + z < n && k[t + z] == key[q]) wt[q] += w[t + z];
-            }
+            if (lead)
+                for (int z = t + 1; z < n && k[z] == key[q]; ++z) wt[q] += w[z];
         }
         const uint64_t m = __ballot(lead) & group;
         if (lead) to[q] = done + (int)__popcll(m & lanemask_lt());
