@@ -276,6 +276,24 @@ __device__ __forceinline__ bool arrive_last(unsigned *cnt) {
     return true;
 }
 
+// The same where all that the last block reads of the others is what their
+// thread 0 wrote with agent-scope stores, and it reads that with agent-scope
+// loads: no cache is written back or invalidated (2 to 3 us of a small grid).
+__device__ __forceinline__ bool arrive_last_relaxed(unsigned *cnt) {
+    const unsigned nb = gridDim.x, g = blockIdx.x / ARRIVE_GROUP;
+    const unsigned ng = (nb + ARRIVE_GROUP - 1) / ARRIVE_GROUP;
+    const unsigned gsize = g + 1 < ng ? ARRIVE_GROUP : nb - g * ARRIVE_GROUP;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the stores are in memory
+    unsigned old = __hip_atomic_fetch_add(&cnt[1 + g], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (old != gsize - 1) return false;
+    __hip_atomic_store(&cnt[1 + g], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    old = __hip_atomic_fetch_add(&cnt[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (old != ng - 1) return false;
+    __hip_atomic_store(&cnt[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" ::: "memory");
+    return true;
+}
+
 // Block sums of K per-thread values, valid in thread 0 (two barriers).
 // sh: K * (blockDim.x / WAVE) entries.
 template <int K>
@@ -357,6 +375,65 @@ __device__ __forceinline__ void block_append3(int bin, int32_t val, int32_t *con
     __syncthreads();
 }
 
+// Inclusive scan of a 32-bit value over the wave, in data-parallel moves (no
+// trip through LDS): within rows of 16 lanes, then across them.
+__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // from 1 lane below
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // lane 15 to the next row
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // lane 31 to the upper half
+    return x;
+}
+
+// Exclusive prefixes of a block's items, wave by wave: item k < K of lane i of
+// wave w is number (w * K + k) * WAVE + i, so that loads and stores of an item
+// by a wave are one run of memory (with consecutive items per thread each of
+// them touched a line per lane) and short inputs spread over all waves.  v is
+// zero past K.  sh: blockDim.x / WAVE values.  Returns the block's sum; two
+// barriers.
+template <int ITEMS>
+__device__ __forceinline__ int64_t block_prefixes(const int64_t (&v)[ITEMS], int64_t (&pre)[ITEMS],
+                                                  int64_t *sh, int K = ITEMS) {
+    bool wide = false;
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) wide = wide || (uint64_t)v[k] >> 24;
+    int64_t run = 0;
+    if (!__ballot(wide)) {   // a wave's sum fits 30 bits
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            if (k < K) {
+                const uint32_t inc = wave_incl_scan_u32((uint32_t)v[k]);
+                pre[k] = run + (inc - (uint32_t)v[k]);
+                run += (uint32_t)__builtin_amdgcn_readlane((int)inc, WAVE - 1);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            if (k < K) {
+                const int64_t inc = wave_incl_scan(v[k]);
+                pre[k] = run + inc - v[k];
+                run += __shfl(inc, WAVE - 1, WAVE);
+            }
+        }
+    }
+    const int w = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
+    __syncthreads();   // sh may still be read by a previous use
+    if (lane_id() == 0) sh[w] = run;
+    __syncthreads();
+    int64_t before = 0, all = 0;
+    for (int i = 0; i < nw; ++i) {
+        const int64_t x = sh[i];
+        before += i < w ? x : 0;
+        all += x;
+    }
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) pre[k] += before;
+    return all;
+}
+
 // ---------------------------------------------------------------------------
 // Generic exclusive scan with a device-side length, two kernels.
 // F: size() -> int64 (< 0: skip the whole scan), operator()(i) -> int64
@@ -388,10 +465,11 @@ __global__ void __launch_bounds__(BLOCK) scan_reduce_k(F f, int64_t *ws, unsigne
             if (idx < n) s += f(idx);
         }
         s = block_sum(s, sh);
-        if (threadIdx.x == 0) partials[t] = s;
+        if (threadIdx.x == 0)
+            __hip_atomic_store(&partials[t], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    if (threadIdx.x == 0) last = arrive_last(arr);
+    if (threadIdx.x == 0) last = arrive_last_relaxed(arr);
     __syncthreads();
     if (!last) return;
     // exclusive scan of the tile sums, in chunks of blockDim.x
@@ -420,27 +498,23 @@ __global__ void __launch_bounds__(BLOCK) scan_apply_k(F f, W w, const int64_t *w
     const int64_t tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
     const auto wb = w.bind();
     for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
-        // each thread owns SCAN_ITEMS consecutive items
-        int64_t first = t * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
-        int64_t vals[SCAN_ITEMS];
-        int64_t s = 0;
+        const int64_t first = t * SCAN_TILE + (threadIdx.x / WAVE) * (SCAN_ITEMS * WAVE) + lane_id();
+        int64_t vals[SCAN_ITEMS], pre[SCAN_ITEMS];
 #pragma unroll
         for (int i = 0; i < SCAN_ITEMS; ++i) {
-            int64_t idx = first + i;
+            const int64_t idx = first + i * WAVE;
             vals[i] = idx < n ? f(idx) : 0;
-            s += vals[i];
         }
         typename W::Pre pf[SCAN_ITEMS];
 #pragma unroll
         for (int i = 0; i < SCAN_ITEMS; ++i)
-            if (first + i < n) pf[i] = wb.prefetch(first + i, vals[i]);
-        int64_t tot;
-        int64_t pre = block_excl_scan(s, sh, &tot) + partials[t];
+            if (first + i * WAVE < n) pf[i] = wb.prefetch(first + i * WAVE, vals[i]);
+        const int64_t tile0 = partials[t];
+        block_prefixes(vals, pre, sh);
 #pragma unroll
         for (int i = 0; i < SCAN_ITEMS; ++i) {
-            int64_t idx = first + i;
-            if (idx < n) wb(idx, pre, vals[i], pf[i]);
-            pre += vals[i];
+            const int64_t idx = first + i * WAVE;
+            if (idx < n) wb(idx, tile0 + pre[i], vals[i], pf[i]);
         }
     }
 }
@@ -463,17 +537,14 @@ __device__ __forceinline__ void scan_one_block(F f, W w, int64_t *total, int64_t
     int &go = *go_p;
     const int64_t n = f.size();
     if (n < 0) return;
-    const int64_t first = (int64_t)threadIdx.x * ONE_SCAN_ITEMS;
     if (n <= ONE_SCAN_CHUNK) {
-        int64_t vals[ONE_SCAN_ITEMS];
-        int64_t s = 0;
+        const int K = (int)((n + ONE_SCAN_THREADS - 1) / ONE_SCAN_THREADS);   // items per thread
+        const int64_t first = (threadIdx.x / WAVE) * (K * WAVE) + lane_id();
+        int64_t vals[ONE_SCAN_ITEMS], pre[ONE_SCAN_ITEMS];
 #pragma unroll
-        for (int i = 0; i < ONE_SCAN_ITEMS; ++i) {
-            vals[i] = first + i < n ? f(first + i) : 0;
-            s += vals[i];
-        }
-        int64_t tot;
-        int64_t pre = block_excl_scan(s, sh, &tot);
+        for (int i = 0; i < ONE_SCAN_ITEMS; ++i)
+            vals[i] = i < K && first + i * WAVE < n ? f(first + i * WAVE) : 0;
+        const int64_t tot = block_prefixes(vals, pre, sh, K);
         if (threadIdx.x == 0) {
             if (total) *total = tot;
             f.post(tot);
@@ -485,14 +556,13 @@ __device__ __forceinline__ void scan_one_block(F f, W w, int64_t *total, int64_t
         typename W::Pre pf[ONE_SCAN_ITEMS];
 #pragma unroll
         for (int i = 0; i < ONE_SCAN_ITEMS; ++i)
-            if (first + i < n) pf[i] = wb.prefetch(first + i, vals[i]);
+            if (i < K && first + i * WAVE < n) pf[i] = wb.prefetch(first + i * WAVE, vals[i]);
 #pragma unroll
-        for (int i = 0; i < ONE_SCAN_ITEMS; ++i) {
-            if (first + i < n) wb(first + i, pre, vals[i], pf[i]);
-            pre += vals[i];
-        }
+        for (int i = 0; i < ONE_SCAN_ITEMS; ++i)
+            if (i < K && first + i * WAVE < n) wb(first + i * WAVE, pre[i], vals[i], pf[i]);
         return;
     }
+    const int64_t first = (threadIdx.x / WAVE) * (ONE_SCAN_ITEMS * WAVE) + lane_id();
     int64_t s = 0;
     for (int64_t i = threadIdx.x; i < n; i += blockDim.x) s += f(i);
     int64_t tot;
@@ -507,25 +577,21 @@ __device__ __forceinline__ void scan_one_block(F f, W w, int64_t *total, int64_t
     const auto wb = w.bind();
     int64_t run = 0;
     for (int64_t base = 0; base < n; base += ONE_SCAN_CHUNK) {
-        int64_t vals[ONE_SCAN_ITEMS];
+        int64_t vals[ONE_SCAN_ITEMS], pre[ONE_SCAN_ITEMS];
         typename W::Pre pf[ONE_SCAN_ITEMS];
-        int64_t t = 0;
 #pragma unroll
         for (int i = 0; i < ONE_SCAN_ITEMS; ++i) {
-            const int64_t idx = base + first + i;
+            const int64_t idx = base + first + i * WAVE;
             vals[i] = idx < n ? f(idx) : 0;
-            t += vals[i];
         }
 #pragma unroll
         for (int i = 0; i < ONE_SCAN_ITEMS; ++i)
-            if (base + first + i < n) pf[i] = wb.prefetch(base + first + i, vals[i]);
-        int64_t ctot;
-        int64_t pre = block_excl_scan(t, sh, &ctot) + run;
+            if (base + first + i * WAVE < n) pf[i] = wb.prefetch(base + first + i * WAVE, vals[i]);
+        const int64_t ctot = block_prefixes(vals, pre, sh);
 #pragma unroll
         for (int i = 0; i < ONE_SCAN_ITEMS; ++i) {
-            const int64_t idx = base + first + i;
-            if (idx < n) wb(idx, pre, vals[i], pf[i]);
-            pre += vals[i];
+            const int64_t idx = base + first + i * WAVE;
+            if (idx < n) wb(idx, run + pre[i], vals[i], pf[i]);
         }
         run += ctot;
     }
