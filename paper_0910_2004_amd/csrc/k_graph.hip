@@ -786,16 +786,16 @@ __device__ __forceinline__ void up_finalize(int32_t k, uint32_t eps_num, uint32_
 }
 
 // The cut over entry tiles; grid blocks walk the tiles of all levels of the
-// table.  Large levels are bound by the row searches and the tile's chain of
-// loads (R-MAT scale 22: 2.9 ms over all levels, the entries' bytes 0.7 ms at
-// copy rate), not by the gathers of part: with a byte per node instead of 32
-// bits 2.9 as well.  Rows of eight consecutive entries of a thread by one
-// search and a walk: 2.7 with bytes, 3.6 without, slower on R-MAT scale 18.
+// table.  Large levels are bound by lines: R-MAT scale 22, all levels, moves
+// 15.6 GB of them (the entries are 5 GB, the gathers of part the rest), at 64
+// registers and eight waves a SIMD in 3.1 ms, at seven in 3.5.  A byte per node
+// instead of 32 bits did not move fewer; rows of eight consecutive entries of
+// a thread by one search and a walk took 3.6 ms and more on R-MAT scale 18.
 // LAST (one level, small grids): the block that finishes last finalizes;
 // otherwise up_finalize_k runs next (a release per block costs more on large
 // grids).
 template <bool LAST>
-__global__ void __launch_bounds__(BLOCK) up_entries_k(UpTable T, int32_t k, uint32_t eps_num,
+__global__ void __launch_bounds__(BLOCK, 8) up_entries_k(UpTable T, int32_t k, uint32_t eps_num,
                                                       uint32_t eps_den, uint64_t *bw, uint64_t *acc,
                                                       unsigned *arrive, uint64_t *block_w_out,
                                                       kappa_cut_result *res) {
