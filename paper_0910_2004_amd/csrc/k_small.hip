@@ -283,7 +283,9 @@ __global__ void __launch_bounds__(SL_THREADS) small_levels_k(Ctx c, int l0) {
             for (int v = tid; v <= n; v += SL_THREADS) s.xadj[v] = (uint16_t)x[v];
             __syncthreads();
         }
-        bool deep = false;
+        // a row too long, or (unchecked input) offsets that are none: the staged
+        // entries have to fit
+        bool deep = tid == 0 && (s.xadj[0] != 0 || s.xadj[n] != s.nnz);
         for (int v = tid; v < n; v += SL_THREADS) {
             const int d = s.xadj[v + 1] - s.xadj[v];
             deep = deep || d < 0 || d > SMALL_DEG;

@@ -85,3 +85,14 @@ def test_mixed_rows(make):
     perm = np.random.default_rng(1).permutation(g.n).astype(np.int32)
     got = graph_np(K.kappa_relabel(dev(g), torch.from_numpy(perm).cuda()))
     assert_graph_equal(got, relabel(g, perm))
+
+
+def test_row_of_more_than_24_bits():
+    # the offsets' scan adds values past 2^24 in 64 bits
+    import torch
+    from workloads import star_graph
+    g = star_graph((1 << 24) + 5)
+    perm = ((np.arange(g.n, dtype=np.int64) * 5 + 3) % g.n).astype(np.int32)
+    assert g.n % 5
+    got = graph_np(K.kappa_relabel(dev(g), torch.from_numpy(perm).cuda()))
+    assert_graph_equal(got, relabel(g, perm))
