@@ -827,13 +827,22 @@ __global__ void __launch_bounds__(FM_THREADS)
     __shared__ int32_t s_off, s_cnt, s_rows, s_stop, s_pick, s_bc[2];
     __shared__ int64_t s_bw[2], s_bd[2];
     __shared__ unsigned long long s_cut, s_bytes;
+    // entries of the later list: other pairs of the launch append to it, so
+    // that one thread reads the count and the block takes its value (the loops
+    // over the list hold barriers).  Entries of those pairs are none of this
+    // one's, its own are counted by the next local iteration.
+    __shared__ unsigned long long s_xn;
     __shared__ uint8_t s_in[REFINE_K_MAX];
     const KeyForm<KT> kf(A.gain_bits);
     const int32_t j = blockIdx.x;
     const int32_t ab = A.cpairs[p0 + j], a = ab & 0xffff, b = ab >> 16;
     const int tid = threadIdx.x, wv = tid / WAVE, gl = tid % RG_LANES, grp = tid / RG_LANES;
     const int32_t la = A.blo[a], lb = A.blo[b];
+    auto later_count = [&]() {
+        return __hip_atomic_load(&A.ctl->xn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     if (tid == 0) {
+        s_xn = later_count();
         s_bytes = 0;
         s_off = 0;
         s_rows = 0;
@@ -895,8 +904,7 @@ __global__ void __launch_bounds__(FM_THREADS)
             f.gid[pos] = id;
             f.info[pos] = make_uint4((uint32_t)x0, 0u, c, (uint32_t)(x1 - x0));
         };
-        const unsigned long long xn =
-            __hip_atomic_load(&A.ctl->xn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long xn = s_xn;
         const bool every = xn > (unsigned long long)A.n;   // the later list overflowed
         for (int32_t b0 = 0; b0 < na + nb; b0 += FM_THREADS * FM_ENT) {   // block-uniform
             int32_t v[FM_ENT], pv[FM_ENT];
@@ -1035,6 +1043,7 @@ __global__ void __launch_bounds__(FM_THREADS)
         if (tid == 0) {
             s_cut = 0;
             s_cnt = 0;
+            s_xn = later_count();
             if (t > 0) t0 = wall_clock64();
             s_bytes += 40ull * (unsigned)len + 12ull * (unsigned long long)(s_bd[0] + s_bd[1]);
         }
@@ -1158,8 +1167,7 @@ __global__ void __launch_bounds__(FM_THREADS)
                 if (pos < FM_AREA)
                     rec[pos] = make_uint4(id, dg, (uint32_t)x0, (uint32_t)((uint64_t)x0 >> 32));
             };
-            const unsigned long long xn =
-                __hip_atomic_load(&A.ctl->xn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long xn = s_xn;
             const bool every = xn > (unsigned long long)A.n;   // the later list overflowed
             const int64_t total = every ? A.n : (int64_t)na + nb + (int64_t)xn;
             for (int64_t t1 = 0; t1 < total; t1 += FM_TILE) {   // block-uniform
@@ -1445,9 +1453,7 @@ __global__ void __launch_bounds__(FM_THREADS)
                 // list from before this launch (another pair of this launch may
                 // be about to list one: then it is listed twice), while it has
                 // room; beyond n entries it stands for every node.
-                if (__hip_atomic_load(&A.ctl->xn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >
-                    (unsigned long long)A.n)
-                    continue;
+                if (later_count() > (unsigned long long)A.n) continue;
                 unsigned long long at = atomicAdd(&A.ctl->xn, 1ull);
                 if (at < (unsigned long long)A.n) A.xlist[at] = v;
                 for (int64_t e = x0; e < x1; ++e) {
