@@ -403,7 +403,8 @@ struct FmArgs {
     int32_t *alist, *ldeg;
     uint64_t *key;          // [2][n]
     int32_t *mlog;          // [2][n] moved nodes, local ids
-    int32_t *loc;           // [n] -1, or a pair's or area's node: its place in alist
+    int32_t *loc;           // [n] -1, or a pair's or area's node: its place in alist (over all
+                            //   pairs of the launch, so that places of two pairs differ)
     int2 *lrow;             // [nnz] rows at the nodes' CSR offsets: {local id, weight}
     int32_t acap;           // pairs and areas of at most acap nodes live in LDS (<= FM_AREA)
     int32_t gain_bits;      // 32-bit keys: bits of gain + bias
@@ -1299,7 +1300,7 @@ __global__ void __launch_bounds__(FM_THREADS)
                 return;
             }
             for (int32_t i = tid; i < N; i += FM_THREADS)
-                A.loc[(uint32_t)alist[i] & 0x7fffffffu] = i;
+                A.loc[(uint32_t)alist[i] & 0x7fffffffu] = off + i;
             __syncthreads();
             // rows inside the area, gains, keys and the first group bests; the
             // queues start with the boundary
@@ -1336,7 +1337,7 @@ __global__ void __launch_bounds__(FM_THREADS)
 #pragma unroll
                     for (int z = 0; z < RG_U; ++z) {
                         pu[z] = u[z] >= 0 ? A.part[u[z]] : -1;
-                        lu[z] = u[z] >= 0 ? A.loc[u[z]] : -1;
+                        lu[z] = u[z] >= 0 ? A.loc[u[z]] - off : -1;
                     }
 #pragma unroll
                     for (int z = 0; z < RG_U; ++z) {
@@ -1344,7 +1345,7 @@ __global__ void __launch_bounds__(FM_THREADS)
                         const bool own = pu[z] == (in_b ? b : a), oth = pu[z] == (in_b ? a : b);
                         gain[z] += oth ? (int64_t)w[z] : (own ? -(int64_t)w[z] : 0);
                         if (oth && !in_b) cut += w[z];
-                        const bool in = (own || oth) && lu[z] >= 0;   // in the area
+                        const bool in = (own || oth) && (uint32_t)lu[z] < (uint32_t)N;   // in the area
                         const uint32_t m = group_ballot(in);
                         if (in) {
                             const uint32_t to = deg[z] + __popc(m & ((1u << gl) - 1u));
