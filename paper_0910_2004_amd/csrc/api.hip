@@ -1032,7 +1032,42 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
     SizeHint hint(n0);
     for (;;) {
         const int l_end = std::min(launched + batch, maxl + 1);
-        int next = l_end;
+        // The batch, launched on q or (go = false) only walked through, which
+        // gives the level it ends at: a replayed sequence launches nothing here,
+        // so that the end must not come from the launching.
+        auto levels_to = [&](bool go, hipStream_t q) {
+            if (begin_only) {
+                if (go) launch_batch_begin(c, launched, q);
+                return launched;
+            }
+            for (int l = launched; l < l_end; ++l) {
+                int32_t nh = hint.at(l);
+                if (l == ext_level) {
+                    if (go)
+                        launch_level_extend(c, l, nh, n0, ext_round,
+                                            EXTEND_ROUNDS << std::min(ext_times, 3), true, q);
+                    continue;
+                }
+                const bool try_tail = tail_on && l >= 1 && nh <= 8 * TAIL_MAX_N;
+                if (go && try_tail) launch_tail(c, l, q);
+                if (try_tail && nh <= 2 * TAIL_MAX_N && l != tail_end) return l;
+                const double eh = deg * nh;
+                if (small_on && l != tail_end && nh <= 4 * SMALL_N && eh <= 4 * SMALL_E) {
+                    if (go) launch_small_levels(c, l, q);
+                    if (2 * nh <= 3 * SMALL_N && 2 * (eh + nh) <= 3 * SMALL_E) return l;
+                }
+                // innerOuter on unit input weights ranks edges by degree
+                // sums, which chains level 0 over many rounds (17 grid rounds
+                // on the random geometric graph of 2^20 nodes); the finisher
+                // completes any remainder
+                int rounds = rounds_for(nh, c.t);
+                if (l == 0 && p->rating == KAPPA_INNER_OUTER) rounds = 18;
+                rounds = std::max(rounds, plan_rounds);
+                if (go) launch_level(c, l, nh, d0.nnz, n0, rounds, q);
+            }
+            return l_end;
+        };
+        const int next = levels_to(false, s);
         uint64_t ratio_bits;
         std::memcpy(&ratio_bits, &hint.ratio, sizeof ratio_bits);
         uint64_t deg_bits;
@@ -1047,43 +1082,7 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
                                            (uint64_t)(int64_t)ext_level, (uint64_t)ext_round,
                                            (uint64_t)begin_only, (uint64_t)small_on, deg_bits,
                                            (uint64_t)plan_rounds};
-        HIPCHK(run_seq(w->c, s, key, [&](hipStream_t q) {
-            if (begin_only) {
-                launch_batch_begin(c, launched, q);
-                next = launched;
-                return;
-            }
-            for (int l = launched; l < l_end; ++l) {
-                int32_t nh = hint.at(l);
-                if (l == ext_level) {
-                    launch_level_extend(c, l, nh, n0, ext_round,
-                                        EXTEND_ROUNDS << std::min(ext_times, 3), true, q);
-                    continue;
-                }
-                const bool try_tail = tail_on && l >= 1 && nh <= 8 * TAIL_MAX_N;
-                if (try_tail) launch_tail(c, l, q);
-                if (try_tail && nh <= 2 * TAIL_MAX_N && l != tail_end) {
-                    next = l;
-                    break;
-                }
-                const double eh = deg * nh;
-                if (small_on && l != tail_end && nh <= 4 * SMALL_N && eh <= 4 * SMALL_E) {
-                    launch_small_levels(c, l, q);
-                    if (2 * nh <= 3 * SMALL_N && 2 * (eh + nh) <= 3 * SMALL_E) {
-                        next = l;
-                        break;
-                    }
-                }
-                // innerOuter on unit input weights ranks edges by degree
-                // sums, which chains level 0 over many rounds (17 grid rounds
-                // on the random geometric graph of 2^20 nodes); the finisher
-                // completes any remainder
-                int rounds = rounds_for(nh, c.t);
-                if (l == 0 && p->rating == KAPPA_INNER_OUTER) rounds = 18;
-                rounds = std::max(rounds, plan_rounds);
-                launch_level(c, l, nh, d0.nnz, n0, rounds, q);
-            }
-        }));
+        HIPCHK(run_seq(w->c, s, key, [&](hipStream_t q) { levels_to(true, q); }));
         const bool tail_last = next < l_end && !begin_only;
         launched = next;
         HIPCHK(hipMemcpyAsync(hc, c.ctrl, sizeof(Control), hipMemcpyDeviceToHost, s));
