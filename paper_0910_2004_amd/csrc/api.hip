@@ -1052,7 +1052,10 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
                 if (go && try_tail) launch_tail(c, l, q);
                 if (try_tail && nh <= 2 * TAIL_MAX_N && l != tail_end) return l;
                 const double eh = deg * nh;
-                if (small_on && l != tail_end && nh <= 4 * SMALL_N && eh <= 4 * SMALL_E) {
+                const bool known = l == hint.known_l;   // nh and eh are the level's own
+                const bool fits = nh <= SMALL_N && eh + nh < SMALL_E + 0.5;
+                if (small_on && l != tail_end &&
+                    (known ? fits : nh <= 4 * SMALL_N && eh <= 4 * SMALL_E)) {
                     if (go) launch_small_levels(c, l, q);
                     if (2 * nh <= 3 * SMALL_N && 2 * (eh + nh) <= 3 * SMALL_E) return l;
                 }
