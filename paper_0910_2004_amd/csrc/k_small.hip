@@ -258,12 +258,24 @@ __global__ void __launch_bounds__(SL_THREADS) small_levels_k(Ctx c, int l0) {
     const int tid = threadIdx.x;
     Control &ctl = s.ctl;   // thread 0's
     if (tid == 0) {
-        const LevelDesc *const L = c.lv + l0;
+        LevelDesc *const L = c.lv + l0;
         ctl = *c.ctrl;
         s.go = !ctl.done && ctl.nlevels == l0 + 1 && L->phase == PH_IDLE && L->mate && L->cmap;
         const int64_t nnz = L->nnz;
         s.n = L->n;
-        s.go = s.go && s.n <= SMALL_N && nnz + s.n <= SMALL_E;
+        if (s.n > SMALL_N || nnz + s.n > SMALL_E) {
+            // a level that does not fit may still be the one to stop at (left to
+            // the grid, that took a read-back and the launches of a batch of
+            // levels, 110 us)
+            const int stop = s.n <= ctl.stop_n ? KAPPA_STOP_SIZE
+                                               : (l0 >= ctl.max_levels ? KAPPA_STOP_MAXLEVEL : KAPPA_STOP_NONE);
+            if (s.go && stop != KAPPA_STOP_NONE) {
+                L->stop = stop;
+                L->phase = PH_STOPPED;
+                c.ctrl->done = 1;
+            }
+            s.go = 0;
+        }
         s.nnz = (int32_t)nnz;
         s.adj = L->adj;
         s.ew = L->ew;

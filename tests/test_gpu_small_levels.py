@@ -101,3 +101,17 @@ def test_arena_grows():
         check_hierarchy(g, 4, 42, 2, k=3)
     finally:
         K.arena_first(0)
+
+
+@pytest.mark.parametrize("stop_n,levels", [(4500, 64), (5001, 64), (2, 1), (2, 0), (2, 2)])
+def test_stops_at_a_level_that_does_not_fit(stop_n, levels):
+    # by nodes (level 0) and by entries (level 1 of the geometric graph)
+    for g in (rgg(5001, seed=1), circulant(5001, 3, 2)):
+        check_hierarchy(g, 0, 42, stop_n, max_levels=levels, k=2)
+    # by a row that grew too long
+    hubs, k, rng = 12, 200, np.random.default_rng(3)
+    e = np.unique(np.repeat(np.arange(hubs), k) * 1000 + rng.integers(0, 900, hubs * k))
+    g = csr_from_edges(hubs + 900, np.concatenate([e // 1000, np.arange(hubs - 1)]),
+                       np.concatenate([hubs + e % 1000, np.arange(1, hubs)]),
+                       np.concatenate([rng.integers(1, 5, len(e)), np.full(hubs - 1, 60)]).astype(np.uint32))
+    check_hierarchy(g, 4, 5, min(stop_n, 900), stall=(0, 1), max_levels=levels, k=2)
