@@ -209,7 +209,7 @@ KERNEL_SYMBOLS = {"pick": r"pick_k<\d, false, 0, (true|false)>", "mate": r"mate_
                   "pick_first": r"pick_k<\d, true, 0, false>", "fill_small": r"fill_small_k",
                   "fill_mid": r"fill_mid_k", "fill_big": r"fill_big_k",
                   "fill_large": r"fill_large_k", "validate_entries": r"validate_entries_k(<(true|false)>)?",
-                  "compact": r"compact_k", "cut_entries": r"up_entries_k<(true|false)>",
+                  "compact": r"compact_k", "cut_entries": r"up_entries_k<(true|false), \d+>",
                   "refine_fm": r"ref_fm_k<.*>"}
 # the sources a kernel's stored counters depend on (they go stale when these change)
 COUNTER_SOURCES = ["paper_0910_2004_amd/csrc/k_level.hip", "paper_0910_2004_amd/csrc/kappa_internal.h",

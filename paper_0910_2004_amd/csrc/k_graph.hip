@@ -791,14 +791,16 @@ __device__ __forceinline__ void up_finalize(int32_t k, uint32_t eps_num, uint32_
 // registers and eight waves a SIMD in 3.1 ms, at seven in 3.5.  A byte per node
 // instead of 32 bits did not move fewer; rows of eight consecutive entries of
 // a thread by one search and a walk took 3.6 ms and more on R-MAT scale 18.
+// N = 1, one level by itself: without the table's look-ups and at the registers
+// the compiler takes (R-MAT scale 21: 297 us a call, 327 through the table and
+// 321 at eight waves; random geometric graph of 2^20 nodes: 76, 81 and 79).
 // LAST (one level, small grids): the block that finishes last finalizes;
 // otherwise up_finalize_k runs next (a release per block costs more on large
 // grids).
-template <bool LAST>
-__global__ void __launch_bounds__(BLOCK, 8) up_entries_k(UpTable T, int32_t k, uint32_t eps_num,
-                                                      uint32_t eps_den, uint64_t *bw, uint64_t *acc,
-                                                      unsigned *arrive, uint64_t *block_w_out,
-                                                      kappa_cut_result *res) {
+template <bool LAST, int N>
+__global__ void __launch_bounds__(BLOCK, N > 1 ? 8 : 1)
+    up_entries_k(UpTableN<N> T, int32_t k, uint32_t eps_num, uint32_t eps_den, uint64_t *bw,
+                 uint64_t *acc, unsigned *arrive, uint64_t *block_w_out, kappa_cut_result *res) {
     __shared__ int64_t s_off[ETILE_ROWS + 1];
     __shared__ uint64_t sh[BLOCK / WAVE + 1];
     __shared__ uint64_t s_acc[3];
@@ -813,18 +815,21 @@ __global__ void __launch_bounds__(BLOCK, 8) up_entries_k(UpTable T, int32_t k, u
                       (unsigned long long)cut);
         cut = 0;
     };
-    for (unsigned tt = blockIdx.x; tt < T.tiles[T.count]; tt += gridDim.x) {   // block-uniform
-        int l = li;
-        while (tt >= T.tiles[l + 1]) ++l;
-        if (l != li) {
-            flush();
-            li = l;
-            L = T.lv[li];
+    const unsigned tiles = T.tiles[N > 1 ? T.count : 1];
+    for (unsigned tt = blockIdx.x; tt < tiles; tt += gridDim.x) {   // block-uniform
+        if constexpr (N > 1) {
+            int l = li;
+            while (tt >= T.tiles[l + 1]) ++l;
+            if (l != li) {
+                flush();
+                li = l;
+                L = T.lv[li];
+            }
         }
         const int32_t *const part = L.part;
         DevGraph g;
         g.n = L.n; g.nnz = L.nnz; g.xadj = L.xadj; g.adj = L.adj; g.ew = L.ew; g.vw = L.vw;
-        const TileCtx t = tile_begin(g, L.tile_row, tt - T.tiles[li], s_off);
+        const TileCtx t = tile_begin(g, L.tile_row, N > 1 ? tt - T.tiles[li] : tt, s_off);
         int32_t vv[ETILE_ITEMS], uu[ETILE_ITEMS];
         uint32_t ww[ETILE_ITEMS];
 #pragma unroll
@@ -880,7 +885,8 @@ static void up_nodes(UpTable &T, const int32_t *base_part, int32_t base_n, bool 
 
 // The table's tile counts (below 2^32: a level has fewer than 2^31 tiles);
 // returns the total.
-static unsigned up_tiles(UpTable &T) {
+template <int N>
+static unsigned up_tiles(UpTableN<N> &T) {
     T.tiles[0] = 0;
     for (int i = 0; i < T.count; ++i) T.tiles[i + 1] = T.tiles[i] + (uint32_t)etiles(T.lv[i].nnz);
     return T.tiles[T.count];
@@ -894,17 +900,22 @@ void launch_cut_level(const DevGraph &g, int32_t *part, int32_t k, uint32_t eps_
     T.l0 = 0;
     T.lv[0] = UpLevel{g.xadj, g.adj, g.ew, g.vw, nullptr, part, tile_row, g.nnz, g.n};
     up_nodes(T, nullptr, 0, true, 0, k, a, s);
-    const unsigned tiles = up_tiles(T);
+    UpOne T1;
+    T1.count = 1;
+    T1.l0 = 0;
+    T1.lv[0] = T.lv[0];
+    const unsigned tiles = up_tiles(T1);
     if (tiles <= UP_LAST_BLOCKS) {
         KAPPA_PROF("up_entries", s);
-        hipLaunchKernelGGL(up_entries_k<true>, dim3(tiles ? tiles : 1), dim3(BLOCK), 0, s, T, k,
-                           eps_num, eps_den, a.bw, a.acc, a.arrive, block_w_out, res);
+        hipLaunchKernelGGL((up_entries_k<true, 1>), dim3(tiles ? tiles : 1), dim3(BLOCK), 0, s, T1,
+                           k, eps_num, eps_den, a.bw, a.acc, a.arrive, block_w_out, res);
         return;
     }
     {
         KAPPA_PROF("up_entries", s);
-        hipLaunchKernelGGL(up_entries_k<false>, dim3(std::min(tiles, UP_ENTRY_BLOCKS)), dim3(BLOCK),
-                           0, s, T, k, eps_num, eps_den, a.bw, a.acc, a.arrive, block_w_out, res);
+        hipLaunchKernelGGL((up_entries_k<false, 1>), dim3(std::min(tiles, UP_ENTRY_BLOCKS)),
+                           dim3(BLOCK), 0, s, T1, k, eps_num, eps_den, a.bw, a.acc, a.arrive,
+                           block_w_out, res);
     }
     KAPPA_PROF("up_finalize", s);
     hipLaunchKernelGGL(up_finalize_k, dim3(1), dim3(BLOCK), 0, s, k, eps_num, eps_den, a.bw, a.acc,
@@ -950,8 +961,8 @@ void launch_way_up(const UpLevel *lv, int32_t nl, uint64_t part_seed, int32_t k,
         }
         if (up_tiles(T) == 0) continue;
         KAPPA_PROF("up_entries", s);
-        hipLaunchKernelGGL(up_entries_k<false>, dim3(std::min(T.tiles[T.count], UP_ENTRY_BLOCKS)),
-                           dim3(BLOCK), 0, s, T, k, eps_num, eps_den, a.bw, a.acc, a.arrive,
+        hipLaunchKernelGGL((up_entries_k<false, UP_TABLE>),
+                           dim3(std::min(T.tiles[T.count], UP_ENTRY_BLOCKS)), dim3(BLOCK), 0, s, T, k, eps_num, eps_den, a.bw, a.acc, a.arrive,
                            (uint64_t *)nullptr, res);
     }
     KAPPA_PROF("up_finalize", s);

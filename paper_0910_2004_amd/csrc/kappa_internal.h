@@ -1043,11 +1043,14 @@ struct UpLevel {
     int32_t n;
 };
 constexpr int UP_TABLE = 24;
-struct UpTable {
-    UpLevel lv[UP_TABLE];
-    uint32_t first[UP_TABLE + 1], tiles[UP_TABLE + 1];
+template <int N>
+struct UpTableN {
+    UpLevel lv[N];
+    uint32_t first[N + 1], tiles[N + 1];
     int32_t count, l0;
 };
+using UpTable = UpTableN<UP_TABLE>;
+using UpOne = UpTableN<1>;   // the cut of one level by itself
 constexpr int BW_SHARDS = 8;
 struct UpAcc {             // nl levels
     uint64_t *bw;      // nl * BW_SHARDS * k
