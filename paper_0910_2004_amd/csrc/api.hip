@@ -2111,6 +2111,8 @@ kappa_status refine_impl(const DevGraph &d, int32_t *part, int32_t k, uint32_t e
         HIPCHK(hipStreamSynchronize(s));
         if (gi == 0 && (rb->ctl.flags & 1u)) return KAPPA_E_RANGE;
         R.max_wd = rb->ctl.max_wd;
+        R.wide = rb->ctl.total > UINT32_MAX || rb->ctl.sum_wd / 2 > UINT32_MAX;
+        if (!refine_gains_fit(R.max_wd)) return KAPPA_E_RANGE;   // 2^60: a row of 2^28 entries
         if (rb->ctl.flags & 2u) {
             if (debug_on()) fprintf(stderr, "kappa: refine: block counts disagree with part\n");
             return KAPPA_E_HIP;

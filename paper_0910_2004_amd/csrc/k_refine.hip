@@ -31,6 +31,7 @@
 // not depend on the order of reductions or of the lists: it is bit-exact
 // with the sequential definition.
 #include <algorithm>
+#include <type_traits>
 
 #include "kappa_internal.h"
 
@@ -99,7 +100,7 @@ __device__ __forceinline__ void wave_rows(int32_t v, int64_t x0, int64_t x1, F &
 }
 
 // block weights, node counts and degree sums, c(V), max c(v), the largest
-// weighted degree; flags a block id outside [0, k).  Also clears the search
+// weighted degree and the sum of all; flags a block id outside [0, k).  Also clears the search
 // scratch that starts empty.
 __global__ void __launch_bounds__(RQ_THREADS)
     ref_weights_k(const int64_t *__restrict__ xadj, const uint32_t *__restrict__ ew,
@@ -108,12 +109,12 @@ __global__ void __launch_bounds__(RQ_THREADS)
                   RefineCtl *ctl) {
     __shared__ unsigned long long s_w[REFINE_K_MAX], s_d[REFINE_K_MAX];
     __shared__ int32_t s_c[REFINE_K_MAX];
-    __shared__ unsigned long long s_tot, s_max, s_wd;
+    __shared__ unsigned long long s_tot, s_max, s_wd, s_sum;
     __shared__ uint32_t s_bad;
     for (int i = threadIdx.x; i < k; i += blockDim.x) { s_w[i] = 0; s_d[i] = 0; s_c[i] = 0; }
-    if (threadIdx.x == 0) { s_tot = 0; s_max = 0; s_wd = 0; s_bad = 0; }
+    if (threadIdx.x == 0) { s_tot = 0; s_max = 0; s_wd = 0; s_sum = 0; s_bad = 0; }
     __syncthreads();
-    unsigned long long tot = 0, mx = 0, wd = 0;
+    unsigned long long tot = 0, mx = 0, wd = 0, all = 0;
     for (int64_t v0 = (int64_t)blockIdx.x * blockDim.x; v0 < n;
          v0 += (int64_t)gridDim.x * blockDim.x) {   // block-uniform
         const int64_t v = v0 + threadIdx.x;
@@ -147,6 +148,7 @@ __global__ void __launch_bounds__(RQ_THREADS)
 #pragma unroll
                           for (int q = 0; q < ROW_CHUNK; ++q) sum += w[q];
                       }
+                      all += sum;
                       if (step > 1) sum = wave_sum(sum);
                       wd = sum > wd ? sum : wd;
                   });
@@ -154,10 +156,12 @@ __global__ void __launch_bounds__(RQ_THREADS)
     tot = wave_sum(tot);
     mx = wave_max(mx);
     wd = wave_max(wd);
+    all = wave_sum(all);
     if (lane_id() == 0) {
         atomicAdd(&s_tot, tot);
         atomicMax(&s_max, mx);
         atomicMax(&s_wd, wd);
+        atomicAdd(&s_sum, all);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < k; i += blockDim.x) {
@@ -171,6 +175,7 @@ __global__ void __launch_bounds__(RQ_THREADS)
         atomicAdd(&ctl->total, s_tot);
         atomicMax(&ctl->max_node, s_max);
         atomicMax(&ctl->max_wd, s_wd);
+        atomicAdd(&ctl->sum_wd, s_sum);
         if (s_bad) atomicOr(&ctl->flags, 1u);
     }
 }
@@ -411,6 +416,10 @@ struct FmArgs {
     RefineCtl *ctl;
 };
 
+// weights of blocks and cuts in a search
+template <bool WIDE>
+using SumOf = std::conditional_t<WIDE, uint64_t, uint32_t>;
+
 // a finished search, published for the adoption
 struct RunState {
     int64_t best_imb, best_cut, best_w[2];
@@ -422,14 +431,16 @@ struct RunState {
 // queued, or moved; nodes outside the search area count as moved).  Queued
 // keys of one side order by gain, then hash; none is 0.  Gains lie within
 // the largest weighted degree, so 32 bits take them with at least 12 hash
-// bits on most graphs (the caller's choice); 64 bits always do: gains stay
-// below 2^32 in magnitude, which leaves 28 hash bits.
+// bits on most graphs (the caller's choice); 64 bits do where the edge
+// weights sum to less than 2^32: gains stay below that in magnitude, which
+// leaves 28 hash bits.  WIDE, for sums of 2^32 and more: 64 bits take gains
+// below 2^60 and the hash bits that those leave, at the last none.
 constexpr int ST_QUEUED = 1, ST_MOVED = 2, ST_SIDE = 4, ST_MASK = 7;
-constexpr int KEY32_GAIN_MAX_BITS = 17;
-template <class KT>
+constexpr int KEY32_GAIN_MAX_BITS = 17, KEY64_GAIN_MAX_BITS = 61;
+template <class KT, bool WIDE>
 struct KeyForm;
 template <>
-struct KeyForm<uint32_t> {
+struct KeyForm<uint32_t, false> {
     int shift;        // of the gain
     int64_t bias;
     __device__ explicit KeyForm(int gain_bits) : shift(32 - gain_bits), bias((int64_t)1 << (gain_bits - 1)) {}
@@ -441,7 +452,19 @@ struct KeyForm<uint32_t> {
     __device__ uint32_t step(uint32_t k, int64_t d) const { return k + ((uint32_t)d << shift); }
 };
 template <>
-struct KeyForm<uint64_t> {
+struct KeyForm<uint64_t, true> {
+    int shift;
+    int64_t bias;
+    __device__ explicit KeyForm(int gain_bits) : shift(64 - gain_bits), bias((int64_t)1 << (gain_bits - 1)) {}
+    __device__ uint64_t make(int64_t gain, uint64_t h, uint32_t st) const {
+        const int hb = shift - 3;
+        return ((uint64_t)(gain + bias) << shift) | (hb > 0 ? h >> (64 - hb) << 3 : 0) | st;
+    }
+    __device__ int64_t gain(uint64_t k) const { return (int64_t)(k >> shift) - bias; }
+    __device__ uint64_t step(uint64_t k, int64_t d) const { return k + ((uint64_t)d << shift); }
+};
+template <>
+struct KeyForm<uint64_t, false> {
     static constexpr int shift = 31;
     static constexpr int64_t bias = (int64_t)1 << 32;
     __device__ explicit KeyForm(int) {}
@@ -563,21 +586,22 @@ __device__ __forceinline__ void lds_max(uint64_t *p, uint64_t v) {
 // search for the winner in its group, and one read of its row, the neighbours'
 // state being in LDS: no barrier, and at most one memory access on the chain.
 // Equal keys are told apart by the whole hash and the id in a rare second
-// pass.  Weights of blocks and cuts fit 32 bits (the sums of all weights do),
-// and (imbalance, cut) orders as (the heavier block's weight if above L_max
+// pass.  Weights of blocks and cuts fit 32 bits where the sums of all weights do
+// (WIDE: 64), and (imbalance, cut) orders as (the heavier block's weight if above L_max
 // else 0, cut).  What only the end needs (weights and counts of the best
 // state, degrees) is taken from the log of moves afterwards.
 // MODE 0: everything in memory; 1: state on chip, rows in memory; 2: rows on
 // chip too.  On chip the keys are padded with zeros.
-template <class KT, int MODE>
+template <class KT, bool WIDE, int MODE>
 __device__ __forceinline__ void fm_search(const FmArgs &A, const FmLds<KT> &f, KT *gb, RunState &R,
                                           int r, int32_t off, int32_t N, int32_t qn, int gsh,
-                                          uint64_t rseed, int64_t S, int64_t L, uint32_t w0,
-                                          uint32_t w1, int32_t c0, int32_t c1, uint32_t cut,
+                                          uint64_t rseed, int64_t S, int64_t L, SumOf<WIDE> w0,
+                                          SumOf<WIDE> w1, int32_t c0, int32_t c1, SumOf<WIDE> cut,
                                           unsigned long long &bytes) {
     constexpr bool CHIP = MODE > 0;
     using Row = RowForm<KT>;
-    const KeyForm<KT> kf(A.gain_bits);
+    using W = SumOf<WIDE>;
+    const KeyForm<KT, WIDE> kf(A.gain_bits);
     const int lane = lane_id();
     KT *const gkey = (KT *)(A.key + (size_t)r * A.n + off);
     KT *const skey = r ? f.key1 : f.key0;
@@ -602,13 +626,13 @@ __device__ __forceinline__ void fm_search(const FmArgs &A, const FmLds<KT> &f, K
         }
         return __builtin_amdgcn_readfirstlane(at);
     };
-    const uint32_t sw0 = w0, sw1 = w1;
+    const W sw0 = w0, sw1 = w1;
     // since * alpha_den > alpha_num * smaller, S * w > L
     const int32_t patience = (int32_t)min<int64_t>(
         (int64_t)A.alpha_num * min(c0, c1) / (int64_t)A.alpha_den, INT32_MAX);
-    const uint32_t wmax = (uint32_t)min<int64_t>(L / S, (int64_t)UINT32_MAX);
-    uint32_t mx = max(w0, w1), over = mx > wmax ? mx : 0u;
-    uint32_t best_over = over, best_cut = cut;
+    const W wmax = (W)min<int64_t>(L / S, WIDE ? INT64_MAX : (int64_t)UINT32_MAX);
+    W mx = max(w0, w1), over = mx > wmax ? mx : (W)0;
+    W best_over = over, best_cut = cut;
     int32_t m = 0, kept = 0, since = 0;
     uint64_t sum_q = 0;
     for (;;) {
@@ -686,12 +710,12 @@ __device__ __forceinline__ void fm_search(const FmArgs &A, const FmLds<KT> &f, K
         mlog[m] = node;
         sum_q += (uint32_t)qn;
         ++m;
-        const uint32_t dw = from ? cv : 0u - cv;   // to block a
+        const W dw = from ? (W)cv : (W)0 - cv;   // to block a
         w0 += dw;
         w1 -= dw;
-        cut -= (uint32_t)kf.gain(M);
+        cut -= (W)kf.gain(M);
         mx = max(w0, w1);
-        over = mx > wmax ? mx : 0u;
+        over = mx > wmax ? mx : (W)0;
         ++since;
         if (over < best_over || (over == best_over && cut < best_cut)) {
             best_over = over;
@@ -770,7 +794,7 @@ __device__ __forceinline__ void fm_search(const FmArgs &A, const FmLds<KT> &f, K
     // the best state's weights and counts, and the degrees moved, from the log
     // (a moved node's key keeps the side it left)
     uint64_t sum_d = 0;
-    uint32_t out_w = 0, in_w = 0;   // weights kept moves took out of blocks a and b
+    W out_w = 0, in_w = 0;   // weights kept moves took out of blocks a and b
     int32_t out_n = 0, in_n = 0;
     for (int32_t t = lane; t < m; t += WAVE) {
         const int32_t i = mlog[t];
@@ -797,8 +821,8 @@ __device__ __forceinline__ void fm_search(const FmArgs &A, const FmLds<KT> &f, K
     in_n = wave_sum(in_n);
     bytes = 17 * sum_q + 25 * sum_d;
     if (lane == 0) {
-        R.best_w[0] = (int64_t)(uint32_t)(sw0 - out_w + in_w);
-        R.best_w[1] = (int64_t)(uint32_t)(sw1 + out_w - in_w);
+        R.best_w[0] = (int64_t)(W)(sw0 - out_w + in_w);
+        R.best_w[1] = (int64_t)(W)(sw1 + out_w - in_w);
         R.best_imb = pair_imb(R.best_w[0], R.best_w[1], S, L);
         R.best_cut = (int64_t)best_cut;
         R.best_cnt[0] = c0 - out_n + in_n;
@@ -817,7 +841,7 @@ __device__ __forceinline__ void fm_search(const FmArgs &A, const FmLds<KT> &f, K
 // state gathered from memory); way back up of one of 2^16 nodes, k = 64: 311 ->
 // 113 ms, preparation of a pair's searches 41 -> 25 us.  512 threads: with 1024
 // the search spills (1.26 us per step).
-template <class KT>
+template <class KT, bool WIDE>
 __global__ void __launch_bounds__(FM_THREADS)
     ref_fm_k(FmArgs A, int32_t gi, int32_t p0, int32_t np) {
     using Row = RowForm<KT>;
@@ -834,7 +858,7 @@ __global__ void __launch_bounds__(FM_THREADS)
     // one's, its own are counted by the next local iteration.
     __shared__ unsigned long long s_xn;
     __shared__ uint8_t s_in[REFINE_K_MAX];
-    const KeyForm<KT> kf(A.gain_bits);
+    const KeyForm<KT, WIDE> kf(A.gain_bits);
     const int32_t j = blockIdx.x;
     const int32_t ab = A.cpairs[p0 + j], a = ab & 0xffff, b = ab >> 16;
     const int tid = threadIdx.x, wv = tid / WAVE, gl = tid % RG_LANES, grp = tid / RG_LANES;
@@ -1397,16 +1421,17 @@ __global__ void __launch_bounds__(FM_THREADS)
         if (wv < 2) {
             unsigned long long bytes = 0;
             const uint64_t seed = wv ? rs1 : rs0;
-            const uint32_t w0 = (uint32_t)s_bw[0], w1 = (uint32_t)s_bw[1];
+            using W = SumOf<WIDE>;
+            const W w0 = (W)s_bw[0], w1 = (W)s_bw[1], c = (W)start_cut;
             if (chip_rows)
-                fm_search<KT, 2>(A, f, s_gb[wv], rs[wv], wv, off, N, n0, gsh, seed, S, L, w0, w1,
-                                 s_bc[0], s_bc[1], (uint32_t)start_cut, bytes);
+                fm_search<KT, WIDE, 2>(A, f, s_gb[wv], rs[wv], wv, off, N, n0, gsh, seed, S, L, w0,
+                                       w1, s_bc[0], s_bc[1], c, bytes);
             else if (chip)
-                fm_search<KT, 1>(A, f, s_gb[wv], rs[wv], wv, off, N, n0, gsh, seed, S, L, w0, w1,
-                                 s_bc[0], s_bc[1], (uint32_t)start_cut, bytes);
+                fm_search<KT, WIDE, 1>(A, f, s_gb[wv], rs[wv], wv, off, N, n0, gsh, seed, S, L, w0,
+                                       w1, s_bc[0], s_bc[1], c, bytes);
             else
-                fm_search<KT, 0>(A, f, s_gb[wv], rs[wv], wv, off, N, n0, gsh, seed, S, L, w0, w1,
-                                 s_bc[0], s_bc[1], (uint32_t)start_cut, bytes);
+                fm_search<KT, WIDE, 0>(A, f, s_gb[wv], rs[wv], wv, off, N, n0, gsh, seed, S, L, w0,
+                                       w1, s_bc[0], s_bc[1], c, bytes);
             if (lane_id() == 0) atomicAdd(&s_bytes, bytes);
         }
         __syncthreads();
@@ -1511,6 +1536,14 @@ void launch_refine_colouring(const RefineLaunch &R, int parity, hipStream_t s) {
                        R.blist);
 }
 
+// bits of gain + 2^(bits - 1), |gain| at most the largest weighted degree
+static int refine_gain_bits(uint64_t max_wd) {
+    int bits = 2;
+    while (bits < 64 && max_wd >= (1ull << (bits - 1))) ++bits;
+    return bits;
+}
+bool refine_gains_fit(uint64_t max_wd) { return refine_gain_bits(max_wd) <= KEY64_GAIN_MAX_BITS; }
+
 void launch_refine_colour(const RefineLaunch &R, int32_t gi, int32_t c, int32_t p0, int32_t npairs,
                           int parity, hipStream_t s) {
     FmArgs A;
@@ -1526,17 +1559,12 @@ void launch_refine_colour(const RefineLaunch &R, int32_t gi, int32_t c, int32_t 
     A.alist = R.alist; A.ldeg = R.ldeg; A.key = R.key; A.mlog = R.mlog;
     A.loc = R.loc; A.lrow = R.lrow; A.ctl = R.ctl;
     A.acap = R.acap < 0 || R.acap > FM_AREA ? FM_AREA : R.acap;
-    // bits of gain + 2^(bits - 1), |gain| at most the largest weighted degree
-    int bits = 2;
-    while (bits < 64 && R.max_wd >= (1ull << (bits - 1))) ++bits;
-    A.gain_bits = bits;
+    A.gain_bits = refine_gain_bits(R.max_wd);
     KAPPA_PROF("refine_fm", s);
-    if (bits <= KEY32_GAIN_MAX_BITS)
-        hipLaunchKernelGGL(ref_fm_k<uint32_t>, dim3(npairs), dim3(FM_THREADS), 0, s, A, gi, p0,
-                           npairs);
-    else
-        hipLaunchKernelGGL(ref_fm_k<uint64_t>, dim3(npairs), dim3(FM_THREADS), 0, s, A, gi, p0,
-                           npairs);
+    const auto k = R.wide                              ? ref_fm_k<uint64_t, true>
+                   : A.gain_bits <= KEY32_GAIN_MAX_BITS ? ref_fm_k<uint32_t, false>
+                                                        : ref_fm_k<uint64_t, false>;
+    hipLaunchKernelGGL(k, dim3(npairs), dim3(FM_THREADS), 0, s, A, gi, p0, npairs);
 }
 
 }  // namespace kappa

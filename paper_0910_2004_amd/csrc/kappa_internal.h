@@ -1188,6 +1188,7 @@ struct RefineCtl {
     unsigned long long total;     // c(V)
     unsigned long long max_node;  // max_v c(v)
     unsigned long long max_wd;    // the largest weighted degree
+    unsigned long long sum_wd;    // the sum of all (twice the edge weights')
     unsigned long long xn;        // entries of the later boundary list (above n: every node)
     uint32_t flags;               // 1: a block id outside [0, k); 2: block counts disagree with part
     int32_t ncol, npairs, pad;
@@ -1217,11 +1218,13 @@ struct RefineLaunch {
     uint64_t *key;                     // 2 * n
     int2 *lrow;                        // nnz
     uint64_t max_wd;                   // the largest weighted degree (read back)
+    bool wide;                         // c(V) or the sum of the edge weights is 2^32 or more
     int32_t acap;   // largest pair or search area kept on chip (-1: the kernel's maximum)
     RefineCtl *ctl;
 };
 
 void launch_refine_weights(const RefineLaunch &R, hipStream_t s);
+bool refine_gains_fit(uint64_t max_wd);   // a search's keys hold gains of this magnitude
 // Q of the current partition, its greedy colouring and the blocks' node lists
 // (qbits and bcnt must be zero).  parity: which half of bc holds the counts.
 void launch_refine_colouring(const RefineLaunch &R, int parity, hipStream_t s);
