@@ -2047,29 +2047,35 @@ kappa_status refine_impl(const DevGraph &d, int32_t *part, int32_t k, uint32_t e
         int32_t col_off[REFINE_COLOURS + 1];
     };
     Head *head = nullptr;
+    // rows: 8 bytes per entry for the pairs' rows.  Where the device has no room
+    // for them the searches run from the graph's own rows, all in memory.
+    auto layout = [&](Carve &cv, bool rows) {
+        head = cv.get<Head>(1);
+        R.bw = cv.get<int64_t>(k);
+        R.bd = cv.get<int64_t>(k);
+        R.bc = cv.get<int32_t>(2 * k);
+        R.qbits = cv.get<unsigned long long>((int64_t)k * REFINE_QW);
+        R.bcnt = cv.get<int32_t>(2 * k);
+        R.blo = cv.get<int32_t>(k + 1);
+        R.bme = cv.get<int32_t>(k);
+        R.tab = cv.get<uint8_t>((int64_t)k * REFINE_COLOURS);
+        R.cpairs = cv.get<int32_t>(maxp);
+        R.ext = cv.get<uint16_t>(n);
+        R.blist = cv.get<int32_t>(n);
+        R.xlist = cv.get<int32_t>(n);
+        R.loc = cv.get<int32_t>(n);
+        R.alist = cv.get<int32_t>(n);
+        R.ldeg = cv.get<int32_t>(n);
+        R.key = cv.get<uint64_t>(2 * n);
+        R.mlog = cv.get<int32_t>(2 * n);
+        R.lrow = rows ? cv.get<int2>(d.nnz) : nullptr;
+    };
     std::unique_ptr<Workspace> w;
-    if (!carve_workspace(s, w, [&](Carve &cv) {
-            head = cv.get<Head>(1);
-            R.bw = cv.get<int64_t>(k);
-            R.bd = cv.get<int64_t>(k);
-            R.bc = cv.get<int32_t>(2 * k);
-            R.qbits = cv.get<unsigned long long>((int64_t)k * REFINE_QW);
-            R.bcnt = cv.get<int32_t>(2 * k);
-            R.blo = cv.get<int32_t>(k + 1);
-            R.bme = cv.get<int32_t>(k);
-            R.tab = cv.get<uint8_t>((int64_t)k * REFINE_COLOURS);
-            R.cpairs = cv.get<int32_t>(maxp);
-            R.ext = cv.get<uint16_t>(n);
-            R.blist = cv.get<int32_t>(n);
-            R.xlist = cv.get<int32_t>(n);
-            R.loc = cv.get<int32_t>(n);
-            R.alist = cv.get<int32_t>(n);
-            R.ldeg = cv.get<int32_t>(n);
-            R.key = cv.get<uint64_t>(2 * n);
-            R.mlog = cv.get<int32_t>(2 * n);
-            R.lrow = cv.get<int2>(d.nnz);
-        }))
-        return KAPPA_E_NOMEM;
+    if (!carve_workspace(s, w, [&](Carve &cv) { layout(cv, true); })) {
+        w.reset();   // the workspace's lock
+        (void)hipGetLastError();
+        if (!carve_workspace(s, w, [&](Carve &cv) { layout(cv, false); })) return KAPPA_E_NOMEM;
+    }
     R.xadj = d.xadj; R.adj = d.adj; R.ew = d.ew; R.vw = d.vw; R.part = part;
     R.n = d.n; R.k = k; R.eps_num = eps_num; R.eps_den = eps_den; R.seed = p->seed;
     R.alpha_num = p->alpha_num; R.alpha_den = p->alpha_den; R.depth = p->depth;
@@ -2078,7 +2084,7 @@ kappa_status refine_impl(const DevGraph &d, int32_t *part, int32_t k, uint32_t e
     // searches kept in memory.  On chip, row starts are 32-bit.
     const char *qc = getenv("KAPPA_REFINE_QCAP");
     R.acap = qc ? atoi(qc) : -1;
-    if (d.nnz > (int64_t)UINT32_MAX) R.acap = 0;
+    if (d.nnz > (int64_t)UINT32_MAX || !R.lrow) R.acap = 0;
     R.ctl = &head->ctl;
     R.col_off = head->col_off;
     {

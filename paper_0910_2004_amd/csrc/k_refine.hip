@@ -410,7 +410,8 @@ struct FmArgs {
     int32_t *mlog;          // [2][n] moved nodes, local ids
     int32_t *loc;           // [n] -1, or a pair's or area's node: its place in alist (over all
                             //   pairs of the launch, so that places of two pairs differ)
-    int2 *lrow;             // [nnz] rows at the nodes' CSR offsets: {local id, weight}
+    int2 *lrow;             // [nnz] rows at the nodes' CSR offsets: {local id, weight}; null:
+                            //   no memory for them (everything else is in memory then too)
     int32_t acap;           // pairs and areas of at most acap nodes live in LDS (<= FM_AREA)
     int32_t gain_bits;      // 32-bit keys: bits of gain + bias
     RefineCtl *ctl;
@@ -698,9 +699,16 @@ __device__ __forceinline__ void fm_search(const FmArgs &A, const FmLds<KT> &f, K
             MODE == 2 ? f.row + x0 : (const typename Row::E *)(A.lrow + x0);
         typename Row::E e{};
         int2 e2 = make_int2(0, 0);
+        // an entry in memory; without the pair's rows, from the graph's own: a
+        // neighbour outside the area becomes {the node itself, 0}
+        auto entry = [&](int64_t x) {
+            if (A.lrow) return A.lrow[x];
+            const int32_t lu = A.loc[A.adj[x]] - off;
+            return (uint32_t)lu < (uint32_t)N ? make_int2(lu, (int32_t)A.ew[x]) : make_int2(node, 0);
+        };
         if (lane < deg) {   // in flight while the move is booked
             if (CHIP) e = prow[lane];
-            else e2 = A.lrow[x0 + lane];
+            else e2 = entry(x0 + lane);
         }
         {   // every lane writes the same
             const KT k = (M & ~(KT)3) | (KT)ST_MOVED;
@@ -733,7 +741,7 @@ __device__ __forceinline__ void fm_search(const FmArgs &A, const FmLds<KT> &f, K
             if (t0 + lane < deg) {
                 if (t0 > 0) {
                     if (CHIP) e = prow[t0 + lane];
-                    else e2 = A.lrow[x0 + t0 + lane];
+                    else e2 = entry(x0 + t0 + lane);
                 }
                 const int32_t u = CHIP ? Row::id(e) : e2.x;
                 const KT ku = ld_key(u);
@@ -1374,7 +1382,7 @@ __global__ void __launch_bounds__(FM_THREADS)
                         if (in) {
                             const uint32_t to = deg[z] + __popc(m & ((1u << gl) - 1u));
                             if (chip) mrow(x0[z])[to] = Row::make(lu[z], w[z]);
-                            else A.lrow[x0[z] + to] = make_int2(lu[z], (int32_t)w[z]);
+                            else if (A.lrow) A.lrow[x0[z] + to] = make_int2(lu[z], (int32_t)w[z]);
                         }
                         deg[z] += __popc(m);
                     }
@@ -1396,7 +1404,7 @@ __global__ void __launch_bounds__(FM_THREADS)
                         f.key0[i] = k0;
                         f.key1[i] = k1;
                     } else {
-                        A.ldeg[off + i] = (int32_t)deg[z];
+                        A.ldeg[off + i] = (int32_t)(A.lrow ? deg[z] : dg[z]);
                         ((KT *)(A.key + off))[i] = k0;
                         ((KT *)(A.key + (size_t)A.n + off))[i] = k1;
                     }
