@@ -566,10 +566,6 @@ __device__ __forceinline__ uint64_t half_top(uint64_t x) {
     half_max2(x, m0, m1);
     return lane_id() < 32 ? m0 : m1;
 }
-__device__ __forceinline__ void wave_order() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 __device__ __forceinline__ void lds_max(uint32_t *p, uint32_t v) { atomicMax(p, v); }
 __device__ __forceinline__ void lds_max(uint64_t *p, uint64_t v) {
     atomicMax((unsigned long long *)p, (unsigned long long)v);

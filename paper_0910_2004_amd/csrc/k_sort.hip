@@ -81,6 +81,7 @@ __global__ void __launch_bounds__(RS_THREADS) rs_scatter_k(const KT *kin, const 
         const int32_t gpos = threadIdx.x < RS_BINS ? hist[(int64_t)threadIdx.x * tiles + tile] : 0;
 #pragma unroll
         for (int q = 0; q < RS_BINS / WAVE; ++q) wcnt[wv][q * WAVE + lane_id()] = 0;
+        wave_order();   // lanes read what other lanes of the wave stored, here and below
 #pragma unroll
         for (int s = 0; s < RS_ITEMS; ++s) {
             const bool live = i0 + s * WAVE < len;
@@ -93,11 +94,11 @@ __global__ void __launch_bounds__(RS_THREADS) rs_scatter_k(const KT *kin, const 
                 same &= bit ? m : ~m;
             }
             const int before = (int)__popcll(same & lanemask_lt());
-            const int c = wcnt[wv][d];   // LDS operations of a wave keep their order
+            const int c = wcnt[wv][d];
             rank[s] = c + before;
-            __builtin_amdgcn_wave_barrier();
+            wave_order();
             if (live && before == 0) wcnt[wv][d] = c + (int)__popcll(same);
-            __builtin_amdgcn_wave_barrier();
+            wave_order();
         }
         __syncthreads();
         int32_t cnt = 0, incl = 0;

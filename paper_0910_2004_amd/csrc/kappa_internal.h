@@ -876,6 +876,13 @@ __device__ __forceinline__ void wave_sync_lds() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
+// The same order for the compiler alone: a wave's LDS operations keep theirs in
+// the hardware, so that no instruction waits.
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // ===========================================================================
 // Level start (first kernel of a level): stop rules (Section 2 threshold,
 // Section 4), state resets.  Every block takes the same decision from the
