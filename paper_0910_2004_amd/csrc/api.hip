@@ -1086,7 +1086,9 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
                                            (uint64_t)begin_only, (uint64_t)small_on, deg_bits,
                                            (uint64_t)plan_rounds,
                                            // the scratch that a graph with long rows gets
-                                           (uint64_t)hub_graph};
+                                           (uint64_t)hub_graph,
+                                           // a server's own flag, read by its steps
+                                           pkey(bi ? bi->interrupt : nullptr)};
         HIPCHK(run_seq(w->c, s, key, [&](hipStream_t q) { levels_to(true, q); }));
         const bool tail_last = next < l_end && !begin_only;
         launched = next;

@@ -5,7 +5,7 @@ import pytest
 
 import oracle as O
 import paper_0910_2004_amd as K
-from gpu_util import check_hierarchy, dev
+from gpu_util import check_hierarchy, compare_hierarchy, dev
 from workloads import csr_from_edges, grid2d, rgg
 
 pytestmark = pytest.mark.gpu
@@ -68,5 +68,30 @@ def test_scratch_of_long_rows():
                 assert r == ol.rounds, f"graph {i} level {l}: rounds"
                 assert list(p[:63]) == list(ol.round_active[:r][:63]), f"graph {i} level {l}"
                 assert list(d[:63]) == list(ol.round_degree[:r][:63]), f"graph {i} level {l}"
+    finally:
+        K.graphs_enable(False)
+
+
+def test_servers_of_their_own():
+    # steps of equal sizes on one server after another, interrupts among them:
+    # a step watches the flag of its own server
+    gs = [grid2d(60, 50), rgg(5001, seed=4)]
+    hs = [O.coarsen(g, O.EXPANSION_STAR2, 42, 40, 1, 20, 64) for g in gs]
+    dgs = [dev(g) for g in gs]
+    K.graphs_enable(True)
+    try:
+        for rep in range(6):
+            srv = K.Server(O.EXPANSION_STAR2, 42)
+            ids = [srv.admit(d, 40) for d in dgs]
+            done, steps = set(), 0
+            srv.interrupt(rep % 2 == 1)   # level by level
+            while srv.active():
+                done |= set(srv.step())
+                steps += 1
+            print("server", rep, "steps", steps, flush=True)
+            assert done == set(ids)
+            for i, h in zip(ids, hs):
+                compare_hierarchy(srv.take(i), h, check_rounds=False, k=2)
+            del srv
     finally:
         K.graphs_enable(False)
