@@ -1144,25 +1144,13 @@ __global__ void __launch_bounds__(FINISH_THREADS) finish_k(Ctx c, int l, int r_l
         // power-law graphs): one workgroup would crawl through them, so the
         // level goes back to the host for more grid rounds.  The level stays
         // in PH_MATCH; `done` ends this batch of levels.
-        // The same holds for few nodes with long rows: FINISH_DEG entries take
-        // the workgroup about 30 us a round (100 K entries: 90 us), the grid
-        // 24 us with its four launches.
+        // (The pending rows' entries are no measure for it: with a limit of 32768
+        // of them as well, dense graphs went to and fro, geometric of mean degree
+        // 60 with a thousand rounds 18.7 -> 37.2 ms, random of mean degree 100
+        // 3.8 -> 5.3 ms; R-MAT scales 10 to 20 within 1 % with and without.)
         const int32_t pend = s_cnt[r0 & 1][0] + s_cnt[r0 & 1][1] + s_cnt[r0 & 1][2];
-        bool back = F == 0 && st->handoff == -1 && r0 == r_last;
-        if (back && pend <= c.t.finish_max && s_cnt[r0 & 1][2] <= c.t.finish_max_big) {
-            int64_t deg = 0;
-            for (int b = 0; b < 3; ++b) {
-                const PList li = plist(c.ms, g.n, r0 & 1, b);
-                for (int i = threadIdx.x; i < min(s_cnt[r0 & 1][b], g.n); i += FINISH_THREADS)
-                    deg += li.d[i];
-            }
-            deg = block_sum(deg, sh);
-            if (threadIdx.x == 0) s_acc[0] = deg;
-            __syncthreads();
-            back = s_acc[0] > FINISH_DEG;
-            __syncthreads();   // s_acc is used again
-        }
-        if (back) {
+        if (F == 0 && st->handoff == -1 && r0 == r_last &&
+            (pend > c.t.finish_max || s_cnt[r0 & 1][2] > c.t.finish_max_big)) {
             if (threadIdx.x == 0) {
                 c.ctrl->ext_level = l;
                 c.ctrl->ext_round = r_last;
