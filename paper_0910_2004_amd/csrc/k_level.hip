@@ -1889,8 +1889,12 @@ __device__ __forceinline__ void fill_small_body(const Ctx &c, int l, unsigned bi
 }
 // BUF: graphs with long rows (many rows for the class lists) append through
 // the per-wave buffers; others (few list rows) directly.
+// Without them seven waves a SIMD (72 registers; left alone the compiler takes 78
+// and six, and the rows' chains of loads show: path of 10^6 nodes 98 and 84 us,
+// 700 x 700 grid 58 and 50, geometric graph of 2^20 nodes 176 and 159, mean
+// degree 30 68 and 73; eight spill: 92, 55, 188, 77).
 template <bool BUF>
-__global__ void __launch_bounds__(BLOCK) fill_small_k(Ctx c, int l) {
+__global__ void __launch_bounds__(BLOCK, BUF ? 1 : 7) fill_small_k(Ctx c, int l) {
     fill_small_body<BLOCK, true, BUF>(c, l, blockIdx.x, gridDim.x);
 }
 
