@@ -1063,7 +1063,8 @@ __device__ void close_matching(const Ctx &c, LevelDesc *L, bool capped, int grid
     __syncthreads();
     {
         const int w = threadIdx.x / WAVE, nw = NT / WAVE;
-        const int slots = (int)min<int64_t>(s_acc[1], STAT_ROUNDS);
+        // (one slot more than pointed: the round after may have counted rescans)
+        const int slots = (int)min<int64_t>(s_acc[1] + 1, STAT_ROUNDS);
         for (int q = w; q < slots * 5; q += nw) {
             const int i = q / 5, f = q % 5;
             int64_t *p = &st->sstat[i][f][lane_id()];

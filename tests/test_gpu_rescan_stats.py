@@ -62,3 +62,17 @@ def test_zero_without_the_profiler():
     for l in range(len(H) - 1):
         _, rr, rd = H.rescan_stats(l)
         assert not rr.any() and not rd.any()
+
+
+@pytest.mark.parametrize("rating", [O.INNER_OUTER, O.EXPANSION_STAR2, O.WEIGHT])
+def test_levels_keep_their_own_counts(rating):
+    # a level's counts are those of its graph coarsened by itself (level l
+    # matches with the seed of level 0 of a call with seed + l): nothing of the
+    # levels before is left in them
+    for g in (rgg(1 << 15, seed=5), rmat(11, 8, seed=4, wseed=5, wmax=20)):
+        assert int(np.diff(g.xadj).max()) <= 1024   # no chunked rows
+        H = K.kappa_coarsen(dev(g), rating, 7, 64)
+        for l in range(len(H) - 1):
+            A = K.kappa_coarsen(H.level(l).graph, rating, 7 + l, 1, 0, 1, 1)
+            for a, b in zip(A.rescan_stats(0), H.rescan_stats(l)):
+                assert np.array_equal(a, b), f"level {l}: {a} {b}"
