@@ -638,7 +638,8 @@ constexpr int UP_NODE_ITEMS = 4;      // nodes of a thread in flight
 // base_part: the partition of the level above the group's coarsest (base_n
 // nodes); null: the group's coarsest level gets the stand-in partition.
 // given: the (single) level's partition is in place.
-__global__ void __launch_bounds__(BLOCK) up_nodes_k(UpTable T, const int32_t *base_part,
+template <int N>
+__global__ void __launch_bounds__(BLOCK) up_nodes_k(UpTableN<N> T, const int32_t *base_part,
                                                     int32_t base_n, int given, uint64_t part_seed,
                                                     int32_t k, uint64_t *bw, uint64_t *acc,
                                                     uint32_t *flag) {
@@ -646,7 +647,8 @@ __global__ void __launch_bounds__(BLOCK) up_nodes_k(UpTable T, const int32_t *ba
     __shared__ uint64_t sh[BLOCK / WAVE + 1];
     __shared__ uint32_t shm[BLOCK / WAVE];
     int li = 0;   // this block's level
-    while (li + 1 < T.count && blockIdx.x >= T.first[li + 1]) ++li;
+    if constexpr (N > 1)
+        while (li + 1 < T.count && blockIdx.x >= T.first[li + 1]) ++li;
     const UpLevel L = T.lv[li];
     const unsigned bid = blockIdx.x - T.first[li], nb = T.first[li + 1] - T.first[li];
     bw += (int64_t)(T.l0 + li) * BW_SHARDS * k;
@@ -872,13 +874,14 @@ __global__ void __launch_bounds__(BLOCK) up_finalize_k(int32_t k, uint32_t eps_n
 constexpr unsigned UP_LAST_BLOCKS = 64;   // grids up to this size finalize in their last block
 constexpr unsigned UP_ENTRY_BLOCKS = 4096;
 
-static void up_nodes(UpTable &T, const int32_t *base_part, int32_t base_n, bool given,
+template <int N>
+static void up_nodes(UpTableN<N> &T, const int32_t *base_part, int32_t base_n, bool given,
                      uint64_t part_seed, int32_t k, const UpAcc &a, hipStream_t s) {
     T.first[0] = 0;
     for (int i = 0; i < T.count; ++i)
         T.first[i + 1] = T.first[i] + grid_for(T.lv[i].n, BLOCK * UP_NODE_ITEMS, UP_NODE_BLOCKS);
     KAPPA_PROF("up_nodes", s);
-    hipLaunchKernelGGL(up_nodes_k, dim3(T.first[T.count]), dim3(BLOCK),
+    hipLaunchKernelGGL(up_nodes_k<N>, dim3(T.first[T.count]), dim3(BLOCK),
                        (size_t)k * sizeof(uint64_t), s, T, base_part, base_n, given ? 1 : 0,
                        part_seed, k, a.bw, a.acc, a.flag);
 }
@@ -895,26 +898,22 @@ static unsigned up_tiles(UpTableN<N> &T) {
 void launch_cut_level(const DevGraph &g, int32_t *part, int32_t k, uint32_t eps_num,
                       uint32_t eps_den, int32_t *tile_row, const UpAcc &a, uint64_t *block_w_out,
                       kappa_cut_result *res, hipStream_t s) {
-    UpTable T;
+    UpOne T;
     T.count = 1;
     T.l0 = 0;
     T.lv[0] = UpLevel{g.xadj, g.adj, g.ew, g.vw, nullptr, part, tile_row, g.nnz, g.n};
     up_nodes(T, nullptr, 0, true, 0, k, a, s);
-    UpOne T1;
-    T1.count = 1;
-    T1.l0 = 0;
-    T1.lv[0] = T.lv[0];
-    const unsigned tiles = up_tiles(T1);
+    const unsigned tiles = up_tiles(T);
     if (tiles <= UP_LAST_BLOCKS) {
         KAPPA_PROF("up_entries", s);
-        hipLaunchKernelGGL((up_entries_k<true, 1>), dim3(tiles ? tiles : 1), dim3(BLOCK), 0, s, T1,
+        hipLaunchKernelGGL((up_entries_k<true, 1>), dim3(tiles ? tiles : 1), dim3(BLOCK), 0, s, T,
                            k, eps_num, eps_den, a.bw, a.acc, a.arrive, block_w_out, res);
         return;
     }
     {
         KAPPA_PROF("up_entries", s);
         hipLaunchKernelGGL((up_entries_k<false, 1>), dim3(std::min(tiles, UP_ENTRY_BLOCKS)),
-                           dim3(BLOCK), 0, s, T1, k, eps_num, eps_den, a.bw, a.acc, a.arrive,
+                           dim3(BLOCK), 0, s, T, k, eps_num, eps_den, a.bw, a.acc, a.arrive,
                            block_w_out, res);
     }
     KAPPA_PROF("up_finalize", s);
