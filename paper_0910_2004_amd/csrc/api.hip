@@ -1006,12 +1006,16 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
     const bool tail_on = !bi && g_tail_on && c.block_bits < 0;
     int tail_end = -1;   // level at which the previous batch ended on a tail launch
     // Small levels in one workgroup's LDS (k_small.hip), likewise: tried ahead
-    // of each level estimated within a factor 4 of its limits (a launch that
-    // takes nothing costs 3 us, a level it takes saves 50), ending the batch
-    // where the estimate fits or nearly (levels lose entries faster than
-    // nodes; a further level launched for nothing costs 70 us, the read-back
-    // 30).  A row too long for it stays so on coarser levels, so a graph with
-    // one keeps to the grid.
+    // of each level that is known to fit or estimated within a factor 4 of its
+    // limits (a launch that takes nothing costs 3 us, a level it takes saves 50;
+    // 2 and 8 in its place measured the same within 1 %), ending the batch where
+    // the estimate is within 3/2 of them (levels lose entries faster than nodes; a
+    // further level launched for nothing costs 70 us, the read-back 30).  Factors
+    // of 1, 3/2, 2 and 3 for that, us: random geometric graphs of 9001 nodes 702,
+    // 675, 668, 695, of 20001 939, 912, 881, 870, of 2^20 3382, 3348, 3318, 3330;
+    // grids of 150 x 150 793, 821, 836, 832 and 300 x 300 1219, 1194, 1209, 1238.
+    // A row too long for it stays so on coarser levels, so a graph with one keeps
+    // to the grid.
     const bool small_on = !bi && !g_tail_on && c.block_bits < 0 && maxdeg0 <= SMALL_DEG;
     double deg = n0 > 0 ? (double)d0.nnz / n0 : 0.0;   // entries per node of the newest level known
     // a level whose finisher handed it back (CF_EXTEND): the next batch
@@ -1024,7 +1028,9 @@ kappa_status coarsen_attempt(const DevGraph &d0, int32_t maxdeg0, const kappa_co
     // 22), and a level handed back leaves everything launched behind it idle
     // (a level's 40 launches, 160 us and more, against 35 for a read-back).  So
     // they get one level a batch, and each plans the rounds the last one took
-    // and a quarter more.
+    // and a quarter more.  (A mesh with one long row pays the read-backs for
+    // little: a geometric graph with one row of 2000 entries, coarsened, 2.14 ms
+    // in batches of two levels and 2.15 so at 2^17 nodes, 4.77 and 4.39 at 2^20.)
     const bool hub_graph = c.big_blocks > 64;
     int plan_rounds = 0;
     if (hub_graph) batch = bi ? std::min(batch, 2) : 1;
@@ -1608,8 +1614,10 @@ kappa_status match_once(const kappa_graph *g, int32_t rating, uint64_t level_see
     in->l0.cmap = cm;
     in->l0.phase = PH_IDLE;
     launch_init_levels(c.ctrl, c.lv, 2, in->ctrl, in->l0, s);
-    // (a launched round that finds nothing left costs two or four launches, a
-    // hand-back for more rounds 40 us)
+    // A launched round that finds nothing left costs two launches, 3 to 4 us in
+    // all, a hand-back for more rounds 40 us.  12 of them (R-MAT scale 14: 257 us a
+    // call, with 24 306, with 4 280; random geometric graph of 2^20 nodes: 400, 441,
+    // 426); innerOuter chains more (2^20 nodes: 24 and 12 alike, 1.02 ms).
     launch_level_match(c, 0, d.n, d.nnz, rating == KAPPA_INNER_OUTER ? 24 : 12, false, true, s);
     LevelDesc *hl = (LevelDesc *)pinned(sizeof(LevelDesc), PIN_LEVELS);
     Control *hc = (Control *)pinned(sizeof(Control));

@@ -892,8 +892,8 @@ __device__ __forceinline__ void mate_phase(const Ctx &c, const DevGraph &g, Leve
     }
     if (__ballot(bad) && lane_id() == 0) atomicOr(&c.ctrl->flags, (uint32_t)CF_STATE);
     // with the rows this round's pick scanned, where it scans every pending
-    // row (with chunked rows the preparation counts the rows that rescan),
-    // while the profiler asks for them
+    // row (with chunked rows those that rescan are counted for the next round,
+    // below), while the profiler asks for them
     int64_t sums[5] = {point, degs, pairs, scanned, sdeg};
     if (c.rescan_stats) {
         block_sum_n<5>(sums, sh);

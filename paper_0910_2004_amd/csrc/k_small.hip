@@ -9,8 +9,12 @@
 // the entries to merge are in LDS during the contraction; the graph itself is
 // read from global memory (it stays in the XCD's L2 from level to level), so a
 // phase is one chain of loads for all nodes together, between barriers.
-// 64 x 64 grid, 8 levels: 390 us in one launch, 128 for the level of 4096 nodes,
-// 20 for those below 200; the whole call 1.10 -> 0.60 ms.
+// 64 x 64 grid down to 100 nodes, 6 levels: 330 us in one launch, 111 for the
+// level of 4096 nodes, 23 for that of 186; the whole call 0.67 -> 0.40 ms.
+// Levels of 3000 to 4000 nodes that lose few of them take 110 to 210 us here and
+// 75 to 150 on the grid: a loop that ends on two to four such levels can lose 5 %
+// (hubs and leaves, 3500 nodes: 410 and 430 us), one that goes on gains (twelve
+// levels: 3.7 and 1.8 ms).
 //
 // What bounds it is one compute unit's issue rate on the largest levels (four
 // waves a SIMD: a merge costs some hundred instructions per entry) and the

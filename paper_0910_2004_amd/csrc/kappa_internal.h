@@ -1118,8 +1118,6 @@ void launch_serve_extract(const DevGraph &u1, const int32_t *noff1, int32_t coun
                           const int32_t *cmap0, const int32_t *gid0, int32_t n0, int64_t *xadj,
                           int32_t *adj, uint32_t *ew, uint32_t *vw, int32_t *cmap, int64_t *eoff1,
                           int32_t *dmax, hipStream_t s);
-// Copies nodes [a, b) of union level u (entries from ea, nnz of them) with
-// ids made local; cmap/mate (may be null) shifted as well.
 // One graph's level out of a batch level: n nodes of the union from a, nnz
 // entries from ea; ids made local (cmap relative to the graph's first node on
 // the next level, cbase; cmap and mate null on the coarsest level).
