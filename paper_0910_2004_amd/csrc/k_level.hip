@@ -1114,7 +1114,7 @@ __device__ void close_matching(const Ctx &c, LevelDesc *L, bool capped, int grid
 // or after round r_last) with workgroup barriers, then closes the level's
 // matching.
 template <int R, int F = 0>
-__global__ void __launch_bounds__(FINISH_THREADS) finish_k(Ctx c, int l, int r_last) {
+__global__ void __launch_bounds__(FINISH_THREADS) finish_k(Ctx c, int l, int r_last, int by_entries) {
     __shared__ Cand shc[FINISH_THREADS / WAVE];
     __shared__ int64_t sh[5 * (FINISH_THREADS / WAVE) + 1];
     __shared__ int32_t s_cnt[2][4];
@@ -1145,13 +1145,29 @@ __global__ void __launch_bounds__(FINISH_THREADS) finish_k(Ctx c, int l, int r_l
         // power-law graphs): one workgroup would crawl through them, so the
         // level goes back to the host for more grid rounds.  The level stays
         // in PH_MATCH; `done` ends this batch of levels.
-        // (The pending rows' entries are no measure for it: with a limit of 32768
-        // of them as well, dense graphs went to and fro, geometric of mean degree
-        // 60 with a thousand rounds 18.7 -> 37.2 ms, random of mean degree 100
-        // 3.8 -> 5.3 ms; R-MAT scales 10 to 20 within 1 % with and without.)
+        // by_entries (graphs with long rows, whose levels come one or two a batch;
+        // once a level): also few nodes with more than FINISH_DEG entries, which
+        // take the workgroup 30 us a round and the grid 8 to 14.  On any graph, and
+        // each time, dense ones went to and fro and left batches of levels idle:
+        // geometric of mean degree 60, a thousand rounds, 18.7 and 37.2 ms, random
+        // of mean degree 100 3.8 and 5.3.
         const int32_t pend = s_cnt[r0 & 1][0] + s_cnt[r0 & 1][1] + s_cnt[r0 & 1][2];
-        if (F == 0 && st->handoff == -1 && r0 == r_last &&
-            (pend > c.t.finish_max || s_cnt[r0 & 1][2] > c.t.finish_max_big)) {
+        bool back = F == 0 && st->handoff == -1 && r0 == r_last;
+        if (back && pend <= c.t.finish_max && s_cnt[r0 & 1][2] <= c.t.finish_max_big) {
+            int64_t deg = 0;
+            if (by_entries)
+                for (int b = 0; b < 3; ++b) {
+                    const PList li = plist(c.ms, g.n, r0 & 1, b);
+                    for (int i = threadIdx.x; i < min(s_cnt[r0 & 1][b], g.n); i += FINISH_THREADS)
+                        deg += li.d[i];
+                }
+            deg = block_sum(deg, sh);
+            if (threadIdx.x == 0) s_acc[0] = deg;
+            __syncthreads();
+            back = s_acc[0] > FINISH_DEG;
+            __syncthreads();   // s_acc is used again
+        }
+        if (back) {
             if (threadIdx.x == 0) {
                 c.ctrl->ext_level = l;
                 c.ctrl->ext_round = r_last;
@@ -3719,7 +3735,7 @@ static void match_impl(const Ctx &c, int l, int32_t n_hint, int rounds, hipStrea
                 }
                 if (e == hipSuccess) {
                     KAPPA_PROF("match_finish", s);
-                    hipLaunchKernelGGL(finish_k<R>, dim3(1), dim3(FINISH_THREADS), 0, s, c, l, r_cap);
+                    hipLaunchKernelGGL(finish_k<R>, dim3(1), dim3(FINISH_THREADS), 0, s, c, l, r_cap, 0);
                     return;
                 }
                 (void)hipGetLastError();   // not launched: no state changed
@@ -3746,7 +3762,8 @@ static void match_impl(const Ctx &c, int l, int32_t n_hint, int rounds, hipStrea
         }
     }
     KAPPA_PROF("match_finish", s);
-    hipLaunchKernelGGL(finish_k<R>, dim3(1), dim3(FINISH_THREADS), 0, s, c, l, rounds);
+    hipLaunchKernelGGL(finish_k<R>, dim3(1), dim3(FINISH_THREADS), 0, s, c, l, rounds,
+                       c.big_blocks > 64 ? 1 : 0);
 }
 
 // Two-phase matcher: the block phase, a few gap rounds as grid launches (the
@@ -3781,7 +3798,7 @@ static void two_phase_impl(const Ctx &c, int l, int32_t n_hint, hipStream_t s) {
     }
     {
         KAPPA_PROF("gap_finish", s);
-        hipLaunchKernelGGL((finish_k<R, 1>), dim3(1), dim3(FINISH_THREADS), 0, s, c, l, rounds);
+        hipLaunchKernelGGL((finish_k<R, 1>), dim3(1), dim3(FINISH_THREADS), 0, s, c, l, rounds, 0);
     }
     {
         KAPPA_PROF("merge", s);
@@ -3807,7 +3824,7 @@ static void extend_impl(const Ctx &c, int l, int32_t n_hint, int r_from, int cou
         launch_later_round<R>(c, l, r, pg, e, s);
     }
     KAPPA_PROF("match_finish", s);
-    hipLaunchKernelGGL(finish_k<R>, dim3(1), dim3(FINISH_THREADS), 0, s, c, l, r_from + count);
+    hipLaunchKernelGGL(finish_k<R>, dim3(1), dim3(FINISH_THREADS), 0, s, c, l, r_from + count, 0);
 }
 
 void launch_level_extend(const Ctx &c, int l, int32_t n_hint, int32_t n_cap, int r_from,

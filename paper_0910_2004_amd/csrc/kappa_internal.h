@@ -27,6 +27,7 @@ constexpr int TAIL_MAX = 128;
 // pending; otherwise it hands the level back for more grid rounds.
 constexpr int FINISH_MAX = 4096;
 constexpr int FINISH_MAX_BIG = 64;
+constexpr int64_t FINISH_DEG = 32768;   // and (by_entries) entries of the pending rows
 constexpr int EXTEND_ROUNDS = 8;   // doubled on every further hand-back of a level, up to 64
 constexpr int BM_BITS_MAX = 11;     // two-phase matcher: blocks of at most 2^11 nodes
 constexpr int BM_THREADS = 512;     //   matched by one workgroup each
