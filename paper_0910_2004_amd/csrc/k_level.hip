@@ -1758,7 +1758,7 @@ __device__ __forceinline__ void wbuf_add(bool pred, int32_t val, int32_t *buf, i
 //         One rank over all entries and a look at the neighbour took the place
 //         of a search for the first occurrence and a rank among those: level 0
 //         of a random geometric graph of 2^20 nodes, 8.4 M entries, 184 ->
-//         151 us.  What is left is lines, not instructions: with ids in no
+//         144 us.  What is left is lines, not instructions: with ids in no
 //         order the partner's row, the gathers of cmap and the staged row are
 //         most of a gigabyte of 128-byte lines --
 // The contraction phases below are written for `nb` blocks of NT threads
